@@ -94,8 +94,8 @@ enum { SKIPCONV_ACT_NONE = 0, SKIPCONV_ACT_IDENTITY = 1, SKIPCONV_ACT_RELU = 2 }
  * chained successor its residual: r = fl32(y_new - y_old) at the blocks this
  * step updated (fp32, plus its bf16 rounding for bf16 layers) and r = 0 at
  * the blocks only the previous step updated; see skipconv_step_chained.
- * TRANSLATE: allow skipconv_step_translated (a second z slot and two block
- * lists in the workspace); not combinable with EMIT_RESIDUAL.
+ * TRANSLATE: allow skipconv_step_translated (a second z slot in the
+ * workspace); not combinable with EMIT_RESIDUAL.
  * LARGE_GATE_TILES: the split pipeline's gate kernel takes tiles of 32 x 32
  * output sites (instead of 16 x 16 or 8 x 8) when its chunk sums combine in
  * lane groups (see skipconv_gate_tile) and such a tile holds at most 256

@@ -39,11 +39,13 @@ constexpr int kRowsPerTile = 64;
 struct Site {
   int n, oy, ox;
   bool ok;
+  bool fresh;  // computed from x_t alone and assigned: reference frames, exposed blocks
 };
 
+template <bool TRANS>
 __device__ __forceinline__ Site site_of_row(const ConvParams& p, const WorkList& W, long g, long total_rows,
                                             int bb) {
-  Site st{0, 0, 0, false};
+  Site st{0, 0, 0, false, p.reference != 0};
   if (g < total_rows) {
     const int j = (int)(g / bb);
     const int within = (int)(g - (long)j * bb);
@@ -56,6 +58,7 @@ __device__ __forceinline__ Site site_of_row(const ConvParams& p, const WorkList&
     st.oy = bi * p.block + wy;
     st.ox = bj * p.block + (within - wy * p.block);
     st.ok = st.oy < p.h_out && st.ox < p.w_out;
+    if constexpr (TRANS) st.fresh = st.fresh || block_exposed(p, bi, bj);
   }
   return st;
 }
@@ -89,7 +92,8 @@ __device__ __forceinline__ void store_y(void* y, size_t i, float v) {
 
 // ---------------------------------------------------------------- bf16 ----
 
-template <bool FAST, int NTN>
+// TRANS: a translated step (x_{t-1} read shifted, exposed blocks fresh).
+template <bool FAST, int NTN, bool TRANS>
 __global__ void __launch_bounds__(kConvThreads) conv_bf16_kernel(ConvParams p) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r16 = lane & 15, kq = lane >> 4;
@@ -109,19 +113,22 @@ __global__ void __launch_bounds__(kConvThreads) conv_bf16_kernel(ConvParams p) {
 
   for (TileWalk tw(ntiles); tw.t < tw.end; tw.t += tw.step) {
     const long g = (long)tw.t * kRowsPerTile + wave * 16 + r16;
-    const Site st = site_of_row(p, W, g, total_rows, bb);
+    const Site st = site_of_row<TRANS>(p, W, g, total_rows, bb);
     const int iy = st.oy * p.stride - p.pad, ix = st.ox * p.stride - p.pad;
     // old z of the outputs this lane stores, loaded before the product
+    const bool no_prev = p.no_prev || st.fresh;
     const int zrow_mine = st.ok ? (st.n * p.h_out + st.oy) * p.w_out + st.ox : -1;
     int zrow[4];
+    bool keep[4];
     float zold[4][NTN];
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       zrow[v] = __shfl(zrow_mine, kq * 4 + v, 64);
+      keep[v] = TRANS ? !__shfl((int)st.fresh, kq * 4 + v, 64) : !p.reference;
 #pragma unroll
       for (int i = 0; i < NTN; ++i) {
         const int col = i * 16 + r16;
-        const bool ok = zrow[v] >= 0 && col < p.c_out && !p.reference;
+        const bool ok = zrow[v] >= 0 && col < p.c_out && keep[v];
         zold[v][i] = p.z[ok ? (size_t)zrow[v] * p.c_out + col : 0];
       }
     }
@@ -144,7 +151,7 @@ __global__ void __launch_bounds__(kConvThreads) conv_bf16_kernel(ConvParams p) {
           const int y = iy + kh, x = ix + kw;
           in[u] = st.ok && ks < p.ksteps && y >= 0 && y < p.h && x >= 0 && x < p.w;
           const size_t off = in[u] ? ((size_t)(st.n * p.h + y) * p.w + x) * p.c + c0 : 0;
-          const long po = (in[u] && !p.no_prev) ? prev_off(p, st.n, y, x, c0) : -1;
+          const long po = !in[u] || no_prev ? -1 : (TRANS ? prev_off(p, st.n, y, x, c0) : (long)off);
           pin[u] = po >= 0;
           ra[u] = *reinterpret_cast<const uint4*>(xt + off);
           rb[u] = *reinterpret_cast<const uint4*>(xp + (pin[u] ? (size_t)po : 0));
@@ -196,7 +203,7 @@ __global__ void __launch_bounds__(kConvThreads) conv_bf16_kernel(ConvParams p) {
             const int y = iy + kh, x = ix + kw;
             const bool in = st.ok && ks < p.ksteps && kidx < kk && y >= 0 && y < p.h && x >= 0 && x < p.w;
             const size_t off = in ? ((size_t)(st.n * p.h + y) * p.w + x) * p.c + ci : 0;
-            const long po = (in && !p.no_prev) ? prev_off(p, st.n, y, x, ci) : -1;
+            const long po = !in || no_prev ? -1 : (TRANS ? prev_off(p, st.n, y, x, ci) : (long)off);
             ein[u][e] = in;
             epin[u][e] = po >= 0;
             ea[u][e] = xt[off];
@@ -236,7 +243,7 @@ __global__ void __launch_bounds__(kConvThreads) conv_bf16_kernel(ConvParams p) {
         const int col = i * 16 + r16;
         if (col >= p.c_out) continue;
         const size_t idx = (size_t)zrow[v] * p.c_out + col;
-        const float nv = p.reference ? acc[i][v] : zold[v][i] + acc[i][v];
+        const float nv = keep[v] ? zold[v][i] + acc[i][v] : acc[i][v];
         p.z[idx] = nv;
         if (p.act) store_y<uint16_t>(p.y, idx, activate(nv, p.act));
       }
@@ -255,14 +262,18 @@ __global__ void __launch_bounds__(kConvThreads) conv_bf16_kernel(ConvParams p) {
 // everything in flight. Without PZ a tile's z_{t-1} is loaded with its halo.
 // OCC: waves per SIMD the register budget aims for.
 
-// EMIT: the epilogue also writes y_new and the successor's residual; y_old is
-// loaded with z_{t-1}.
-template <int WAVES_M, int WAVES_N, int WM, int WN, int KR = 0, bool PZ = true, int OCC = 2, int KU = 12,
-          int ADB = 2, bool EMIT = false>
-__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) __attribute__((amdgpu_waves_per_eu(EMIT && OCC > 2 ? 2 : OCC)))
+// MODE kEmit: the epilogue also writes y_new and the successor's residual;
+// y_old is loaded with z_{t-1}. MODE kTrans: a translated step; the grid also
+// moves the state of the blocks that are off. (Modes of their own, so that the
+// plain step carries neither's code: with the translated step's in it, the
+// 8 x 8-block build of 64 channels measured 3 % slower.)
+enum HaloMode { kPlain, kEmit, kTrans };
+template <int WAVES_M, int WAVES_N, int WM, int WN, int KR, bool PZ, int OCC, int KU, int ADB, int MODE>
+__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) __attribute__((amdgpu_waves_per_eu(MODE == kEmit && OCC > 2 ? 2 : OCC)))
 conv_halo_kernel(ConvParams p, HaloParams hp) {
   extern __shared__ __attribute__((aligned(16))) uint8_t halo[];
-  typedef HaloConv<WAVES_M, WAVES_N, WM, WN, KR, KU, ADB> HC;
+  constexpr bool EMIT = MODE == kEmit;
+  typedef HaloConv<WAVES_M, WAVES_N, WM, WN, KR, KU, ADB, MODE == kTrans> HC;
   const int tpb = hp.tiles_per_block;
   const WorkList W = work_list(p.counters, p.seg_tiles, p.seg_cap);
   const int ntiles = (int)W.total * tpb;
@@ -281,11 +292,14 @@ conv_halo_kernel(ConvParams p, HaloParams hp) {
     const int n = (int)(blk / per_img);
     const int rem = (int)(blk - (uint32_t)n * per_img);
     const int bi = rem / p.wb, bj = rem - bi * p.wb;
-    return H.tile(n, bi * p.block + band * hp.tr, bj * p.block);
+    return H.tile(n, bi * p.block + band * hp.tr, bj * p.block, p.reference || (MODE == kTrans && block_exposed(p, bi, bj)));
   };
 
   TileWalk tw(ntiles);
-  if (tw.t >= tw.end) return;
+  if (tw.t >= tw.end) {
+    if constexpr (MODE == kTrans) H.move_state();
+    return;
+  }
   HaloTile T = decode(tw.t);
   typename HC::Acc zn;
   typename HC::Yv yn;  // emission: y_old of the next tile (PZ)
@@ -318,6 +332,7 @@ conv_halo_kernel(ConvParams p, HaloParams hp) {
     else H.store(T, acc);
     T = Tn;
   }
+  if constexpr (MODE == kTrans) H.move_state();
 }
 
 // ---------------------------------------------------------------- fp32 ----
@@ -328,7 +343,7 @@ conv_halo_kernel(ConvParams p, HaloParams hp) {
 // The part sums meet in LDS, where wave 0 adds them in part order and updates
 // z. Tap and channel of a k index come from qdiv (exact for these sizes), not
 // from integer divisions.
-template <int NTN>
+template <int NTN, bool TRANS>
 __global__ void __launch_bounds__(kConvThreads) conv_f32_kernel(ConvParams p) {
   // k-steps whose operand (two frames) and weight loads are issued together:
   // every load is unconditional (clamped to element 0 and masked after), so
@@ -352,20 +367,23 @@ __global__ void __launch_bounds__(kConvThreads) conv_f32_kernel(ConvParams p) {
 
   for (TileWalk tw(ntiles); tw.t < tw.end; tw.t += tw.step) {
     const long g = (long)tw.t * kConvF32Rows + r16;
-    const Site st = site_of_row(p, W, g, total_rows, bb);
+    const Site st = site_of_row<TRANS>(p, W, g, total_rows, bb);
     const int iy = st.oy * p.stride - p.pad, ix = st.ox * p.stride - p.pad;
     // old z of the outputs wave 0 stores (site of lane kq * 4 + v, column
     // i * 16 + r16), loaded before the product (other waves read element 0)
+    const bool no_prev = p.no_prev || st.fresh;
     const int zrow_mine = st.ok ? (st.n * p.h_out + st.oy) * p.w_out + st.ox : -1;
     int zrow[4];
+    bool keep[4];
     float zold[4][NTN];
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       zrow[v] = __shfl(zrow_mine, kq * 4 + v, 64);
+      keep[v] = TRANS ? !__shfl((int)st.fresh, kq * 4 + v, 64) : !p.reference;
 #pragma unroll
       for (int i = 0; i < NTN; ++i) {
         const int col = i * 16 + r16;
-        const bool ok = wave == 0 && zrow[v] >= 0 && col < p.c_out && !p.reference;
+        const bool ok = wave == 0 && zrow[v] >= 0 && col < p.c_out && keep[v];
         zold[v][i] = p.z[ok ? (size_t)zrow[v] * p.c_out + col : 0];
       }
     }
@@ -385,7 +403,7 @@ __global__ void __launch_bounds__(kConvThreads) conv_f32_kernel(ConvParams p) {
         const int y = iy + kh, x = ix + kw;
         in[u] = st.ok && ks < ks1 && kidx < kk && y >= 0 && y < p.h && x >= 0 && x < p.w;
         const size_t off = in[u] ? ((size_t)(st.n * p.h + y) * p.w + x) * p.c + ci : 0;
-        const long po = (in[u] && !p.no_prev) ? prev_off(p, st.n, y, x, ci) : -1;
+        const long po = !in[u] || no_prev ? -1 : (TRANS ? prev_off(p, st.n, y, x, ci) : (long)off);
         pin[u] = po >= 0;
         av[u] = xt[off];
         pv[u] = xp[pin[u] ? (size_t)po : 0];
@@ -426,7 +444,7 @@ __global__ void __launch_bounds__(kConvThreads) conv_f32_kernel(ConvParams p) {
           const int col = i * 16 + r16;
           if (col >= p.c_out) continue;
           const size_t idx = (size_t)zrow[v] * p.c_out + col;
-          const float nv = p.reference ? acc[i][v] : zold[v][i] + acc[i][v];
+          const float nv = keep[v] ? zold[v][i] + acc[i][v] : acc[i][v];
           p.z[idx] = nv;
           if (p.act) store_y<float>(p.y, idx, activate(nv, p.act));
         }
@@ -455,7 +473,7 @@ __global__ void __launch_bounds__(kConvThreads) depthwise_kernel(ConvParams p) {
     for (int item = threadIdx.x; item < kRowsPerTile * nchunk; item += kConvThreads) {
       const int row = item / nchunk;
       const int c0 = (item - row * nchunk) * VEC;
-      const Site st = site_of_row(p, W, (long)tw.t * kRowsPerTile + row, total_rows, bb);
+      const Site st = site_of_row<true>(p, W, (long)tw.t * kRowsPerTile + row, total_rows, bb);
       if (!st.ok) continue;
       const int iy = st.oy * p.stride - p.pad, ix = st.ox * p.stride - p.pad;
       float acc[VEC];
@@ -469,7 +487,7 @@ __global__ void __launch_bounds__(kConvThreads) depthwise_kernel(ConvParams p) {
           if (x < 0 || x >= p.w) continue;
           const size_t off = ((size_t)(st.n * p.h + y) * p.w + x) * p.c + c0;
           float a[VEC], b[VEC];
-          const long po = p.no_prev ? -1 : prev_off(p, st.n, y, x, c0);
+          const long po = p.no_prev || st.fresh ? -1 : prev_off(p, st.n, y, x, c0);
           if (VEC == 8) {
             Elem<T>::load8(xt, off, a);
             if (po >= 0) Elem<T>::load8(xp, (size_t)po, b);
@@ -492,7 +510,7 @@ __global__ void __launch_bounds__(kConvThreads) depthwise_kernel(ConvParams p) {
       const size_t zb = ((size_t)(st.n * p.h_out + st.oy) * p.w_out + st.ox) * p.c_out + c0;
 #pragma unroll
       for (int j = 0; j < VEC; ++j) {
-        const float nv = p.reference ? acc[j] : p.z[zb + j] + acc[j];
+        const float nv = st.fresh ? acc[j] : p.z[zb + j] + acc[j];
         p.z[zb + j] = nv;
         if (p.act) store_y<T>(p.y, zb + j, activate(nv, p.act));
       }
@@ -562,6 +580,8 @@ __global__ void __launch_bounds__(kDwThreads) depthwise_halo_kernel(ConvParams p
     const int n = (int)(blk / per_img);
     const int rem = (int)(blk - (uint32_t)n * per_img);
     const int bi = rem / p.wb, bj = rem - bi * p.wb;
+    const bool fresh = p.reference || block_exposed(p, bi, bj);
+    const bool no_prev = p.no_prev || fresh;
     const int oy0 = bi * b + band * hp.tr, ox0 = bj * b;
     const int rows_ok = min(min(hp.tr, b - band * hp.tr), p.h_out - oy0), cols_ok = min(b, p.w_out - ox0);
     const int iy0 = oy0 * s - p.pad, ix0 = ox0 * s - p.pad;
@@ -570,7 +590,7 @@ __global__ void __launch_bounds__(kDwThreads) depthwise_halo_kernel(ConvParams p
     const auto zrs = frame_rsrc(p.z + (size_t)n * zimg, (uint32_t)(zimg * 4));
 
     // old z of a pass of kDwOut (site, chunk) outputs per thread; out-of-range
-    // offsets for outputs outside the tile (and for every output on a reference frame)
+    // offsets for outputs outside the tile (and for every output of a fresh tile)
     floatx4 zo[kDwOut][2];
     uint32_t zoff[kDwOut];
     auto zload = [&](int base) {
@@ -585,7 +605,7 @@ __global__ void __launch_bounds__(kDwThreads) depthwise_halo_kernel(ConvParams p
         for (int hlf = 0; hlf < 2; ++hlf)
           zo[u][hlf] = __builtin_bit_cast(
               floatx4, __builtin_amdgcn_raw_buffer_load_b128(
-                           zrs, p.reference || !ok ? kOutOfRange : zoff[u] + 16 * hlf, 0, 0));
+                           zrs, fresh || !ok ? kOutOfRange : zoff[u] + 16 * hlf, 0, 0));
       }
     };
     auto outputs = [&](int base) {
@@ -611,7 +631,7 @@ __global__ void __launch_bounds__(kDwThreads) depthwise_halo_kernel(ConvParams p
           }
         floatx4 nv[2];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) nv[j >> 2][j & 3] = p.reference ? acc[j] : zo[u][j >> 2][j & 3] + acc[j];
+        for (int j = 0; j < 8; ++j) nv[j >> 2][j & 3] = zo[u][j >> 2][j & 3] + acc[j];
 #pragma unroll
         for (int hlf = 0; hlf < 2; ++hlf)
           __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, nv[hlf]), zrs,
@@ -637,7 +657,7 @@ __global__ void __launch_bounds__(kDwThreads) depthwise_halo_kernel(ConvParams p
         const int y = iy0 + hy, x = ix0 + hx;
         const bool in = idx < total && y >= 0 && y < p.h && x >= 0 && x < p.w;
         const int yp = y - p.sy, xq = x - p.sx;
-        const bool pin = in && !p.no_prev && yp >= 0 && yp < p.h && xq >= 0 && xq < p.w;
+        const bool pin = in && !no_prev && yp >= 0 && yp < p.h && xq >= 0 && xq < p.w;
         ra[u] = __builtin_amdgcn_raw_buffer_load_b128(
             xrs, in ? (uint32_t)(((y * p.w + x) * c + ch * 8) * 2) : kOutOfRange, 0, 0);
         rb[u] = __builtin_amdgcn_raw_buffer_load_b128(
@@ -714,28 +734,25 @@ __global__ void pack_depthwise_kernel(const void* w, float* out, int dtype, int 
   out[i] = dtype == 1 ? bf16_to_f32(static_cast<const uint16_t*>(w)[src]) : static_cast<const float*>(w)[src];
 }
 
-template <bool FAST>
+template <bool FAST, bool TRANS>
 hipError_t launch_conv_bf16(const ConvParams& p, int grid, hipStream_t st) {
   switch (p.ntiles_n) {
-    case 1: hipLaunchKernelGGL((conv_bf16_kernel<FAST, 1>), dim3(grid), dim3(kConvThreads), 0, st, p); break;
-    case 2: hipLaunchKernelGGL((conv_bf16_kernel<FAST, 2>), dim3(grid), dim3(kConvThreads), 0, st, p); break;
-    case 4: hipLaunchKernelGGL((conv_bf16_kernel<FAST, 4>), dim3(grid), dim3(kConvThreads), 0, st, p); break;
-    case 8: hipLaunchKernelGGL((conv_bf16_kernel<FAST, 8>), dim3(grid), dim3(kConvThreads), 0, st, p); break;
-    case 12: hipLaunchKernelGGL((conv_bf16_kernel<FAST, 12>), dim3(grid), dim3(kConvThreads), 0, st, p); break;
-    case 16: hipLaunchKernelGGL((conv_bf16_kernel<FAST, 16>), dim3(grid), dim3(kConvThreads), 0, st, p); break;
+#define SC_X(n) \
+  case n: hipLaunchKernelGGL((conv_bf16_kernel<FAST, n, TRANS>), dim3(grid), dim3(kConvThreads), 0, st, p); break;
+    SC_X(1) SC_X(2) SC_X(4) SC_X(8) SC_X(12) SC_X(16)
+#undef SC_X
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
+template <bool TRANS>
 hipError_t launch_conv_f32(const ConvParams& p, int grid, hipStream_t st) {
   switch (p.ntiles_n) {
-    case 1: hipLaunchKernelGGL((conv_f32_kernel<1>), dim3(grid), dim3(kConvThreads), 0, st, p); break;
-    case 2: hipLaunchKernelGGL((conv_f32_kernel<2>), dim3(grid), dim3(kConvThreads), 0, st, p); break;
-    case 4: hipLaunchKernelGGL((conv_f32_kernel<4>), dim3(grid), dim3(kConvThreads), 0, st, p); break;
-    case 8: hipLaunchKernelGGL((conv_f32_kernel<8>), dim3(grid), dim3(kConvThreads), 0, st, p); break;
-    case 12: hipLaunchKernelGGL((conv_f32_kernel<12>), dim3(grid), dim3(kConvThreads), 0, st, p); break;
-    case 16: hipLaunchKernelGGL((conv_f32_kernel<16>), dim3(grid), dim3(kConvThreads), 0, st, p); break;
+#define SC_X(n) \
+  case n: hipLaunchKernelGGL((conv_f32_kernel<n, TRANS>), dim3(grid), dim3(kConvThreads), 0, st, p); break;
+    SC_X(1) SC_X(2) SC_X(4) SC_X(8) SC_X(12) SC_X(16)
+#undef SC_X
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -743,30 +760,38 @@ hipError_t launch_conv_f32(const ConvParams& p, int grid, hipStream_t st) {
 
 template <int WAVES_M, int WAVES_N, int WM, int WN, int KR, bool PZ, int OCC, int KU, int ADB>
 hipError_t launch_halo_t(const ConvParams& p, const HaloParams& hp, int grid, hipStream_t st) {
+  const dim3 g(grid), b(64 * WAVES_M * WAVES_N);
   if (hp.emit)
-    hipLaunchKernelGGL((conv_halo_kernel<WAVES_M, WAVES_N, WM, WN, KR, PZ, OCC, KU, ADB, true>), dim3(grid),
-                       dim3(64 * WAVES_M * WAVES_N), hp.lds_bytes, st, p, hp);
+    hipLaunchKernelGGL((conv_halo_kernel<WAVES_M, WAVES_N, WM, WN, KR, PZ, OCC, KU, ADB, kEmit>), g, b, hp.lds_bytes,
+                       st, p, hp);
+  else if (p.zsrc)
+    hipLaunchKernelGGL((conv_halo_kernel<WAVES_M, WAVES_N, WM, WN, KR, PZ, OCC, KU, ADB, kTrans>), g, b, hp.lds_bytes,
+                       st, p, hp);
   else
-    hipLaunchKernelGGL((conv_halo_kernel<WAVES_M, WAVES_N, WM, WN, KR, PZ, OCC, KU, ADB>), dim3(grid),
-                       dim3(64 * WAVES_M * WAVES_N), hp.lds_bytes, st, p, hp);
+    hipLaunchKernelGGL((conv_halo_kernel<WAVES_M, WAVES_N, WM, WN, KR, PZ, OCC, KU, ADB, kPlain>), g, b, hp.lds_bytes,
+                       st, p, hp);
   return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_conv(const ConvParams& p, int dtype, bool fast, int grid, hipStream_t st) {
-  if (dtype == 0) return launch_conv_f32(p, grid, st);
-  return fast ? launch_conv_bf16<true>(p, grid, st) : launch_conv_bf16<false>(p, grid, st);
+  const bool trans = p.sy != 0 || p.sx != 0;
+  if (dtype == 0) return trans ? launch_conv_f32<true>(p, grid, st) : launch_conv_f32<false>(p, grid, st);
+  if (fast) return trans ? launch_conv_bf16<true, true>(p, grid, st) : launch_conv_bf16<true, false>(p, grid, st);
+  return trans ? launch_conv_bf16<false, true>(p, grid, st) : launch_conv_bf16<false, false>(p, grid, st);
 }
 
 namespace {
 template <int WAVES_M, int WAVES_N, int WM, int WN, int KR, bool PZ, int OCC, int KU, int ADB>
 int halo_occ_t(const HaloParams& hp) {
-  auto fn = hp.emit ? conv_halo_kernel<WAVES_M, WAVES_N, WM, WN, KR, PZ, OCC, KU, ADB, true>
-                    : conv_halo_kernel<WAVES_M, WAVES_N, WM, WN, KR, PZ, OCC, KU, ADB>;
-  if (hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
-                          hp.lds_bytes) != hipSuccess)
-    return 0;
+  auto fn = hp.emit ? conv_halo_kernel<WAVES_M, WAVES_N, WM, WN, KR, PZ, OCC, KU, ADB, kEmit>
+                    : conv_halo_kernel<WAVES_M, WAVES_N, WM, WN, KR, PZ, OCC, KU, ADB, kPlain>;
+  auto tr = conv_halo_kernel<WAVES_M, WAVES_N, WM, WN, KR, PZ, OCC, KU, ADB, kTrans>;
+  for (auto f : {fn, tr})
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            hp.lds_bytes) != hipSuccess)
+      return 0;
   int blocks = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, fn, 64 * WAVES_M * WAVES_N, hp.lds_bytes) !=
       hipSuccess)

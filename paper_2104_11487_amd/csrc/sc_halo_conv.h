@@ -47,9 +47,10 @@ __device__ __forceinline__ float activate(float v, int act) { return act == 2 ? 
 
 struct HaloTile {
   int n, oy0, ox0, rows_ok, cols_ok, iy0, ix0;
+  bool fresh;  // computed from x_t alone and assigned: reference frames, exposed blocks
 };
 
-template <int WAVES_M, int WAVES_N, int WM, int WN, int KR, int KU, int ADB>
+template <int WAVES_M, int WAVES_N, int WM, int WN, int KR, int KU, int ADB, bool TRANS>
 struct HaloConv {
   static constexpr int kThreads = 64 * WAVES_M * WAVES_N;
   static constexpr int kR = KR ? KR : (WN <= 2 ? 8 : (WN == 3 ? 6 : 4));  // even
@@ -88,8 +89,9 @@ struct HaloConv {
     }
   }
 
-  __device__ HaloTile tile(int n, int oy0, int ox0) const {
+  __device__ HaloTile tile(int n, int oy0, int ox0, bool fresh) const {
     HaloTile T;
+    T.fresh = fresh;
     T.n = n;
     T.oy0 = oy0;
     T.ox0 = ox0;
@@ -118,18 +120,18 @@ struct HaloConv {
   }
 
   // z_{t-1} of a tile in the transposed MFMA output layout; zeros outside the
-  // frame and on a reference frame (none: every piece out of range, so the
+  // frame and on a fresh tile (none: every piece out of range, so the
   // registers are always written)
   // (translated steps: from zsrc at the site shifted back by (zdy, zdx))
   __device__ void load_z(Acc& dst, const HaloTile& T, bool none) const {
-    const auto zrs = p.zsrc ? frame_rsrc(p.zsrc + (size_t)T.n * zimg, (uint32_t)(zimg * 4)) : zres(T);
+    const auto zrs = TRANS ? frame_rsrc(p.zsrc + (size_t)T.n * zimg, (uint32_t)(zimg * 4)) : zres(T);
 #pragma unroll
     for (int i = 0; i < WM; ++i)
 #pragma unroll
       for (int jn = 0; jn < WN; ++jn)
         dst[i][jn] = __builtin_bit_cast(
             floatx4, __builtin_amdgcn_raw_buffer_load_b128(
-                         zrs, p.reference || none ? kOutOfRange : (p.zsrc ? zoff_src(T, i, jn) : zoff(T, i, jn)),
+                         zrs, T.fresh || none ? kOutOfRange : (TRANS ? zoff_src(T, i, jn) : zoff(T, i, jn)),
                          0, 0));
   }
 
@@ -153,6 +155,7 @@ struct HaloConv {
     const uint16_t* xt = static_cast<const uint16_t*>(p.x_t);
     const uint16_t* xp = static_cast<const uint16_t*>(p.x_prev);
     const auto xrs = frame_rsrc(xt + (size_t)T.n * ximg, (uint32_t)(ximg * 2));
+    const bool no_prev = p.no_prev || T.fresh;
     const auto prs = frame_rsrc((p.no_prev ? xt : xp) + (size_t)T.n * ximg, (uint32_t)(ximg * 2));
     const int c = p.c;
     u32x4 ra[KU], rb[KU];
@@ -168,12 +171,15 @@ struct HaloConv {
       const int hy = px / hp.hw, hx = px - hy * hp.hw;
       const int y = T.iy0 + hy, x = T.ix0 + hx;
       const bool in = idx < total && y >= 0 && y < p.h && x >= 0 && x < p.w;
-      const int yp = y - p.sy, xq = x - p.sx;
-      const bool pin = in && !p.no_prev && yp >= 0 && yp < p.h && xq >= 0 && xq < p.w;
-      ra[u] = __builtin_amdgcn_raw_buffer_load_b128(
-          xrs, in ? (uint32_t)(((y * p.w + x) * c + ch * 8) * 2) : kOutOfRange, 0, 0);
-      rb[u] = __builtin_amdgcn_raw_buffer_load_b128(
-          prs, pin ? (uint32_t)(((yp * p.w + xq) * c + ch * 8) * 2) : kOutOfRange, 0, 0);
+      const uint32_t off = in ? (uint32_t)(((y * p.w + x) * c + ch * 8) * 2) : kOutOfRange;
+      uint32_t poff = no_prev ? kOutOfRange : off;
+      if constexpr (TRANS) {
+        const int yp = y - p.sy, xq = x - p.sx;
+        const bool pin = in && !no_prev && yp >= 0 && yp < p.h && xq >= 0 && xq < p.w;
+        poff = pin ? (uint32_t)(((yp * p.w + xq) * c + ch * 8) * 2) : kOutOfRange;
+      }
+      ra[u] = __builtin_amdgcn_raw_buffer_load_b128(xrs, off, 0, 0);
+      rb[u] = __builtin_amdgcn_raw_buffer_load_b128(prs, poff, 0, 0);
     }
 #pragma unroll
     for (int u = 0; u < KU; ++u) {
@@ -328,6 +334,50 @@ struct HaloConv {
             u32x2v{f32_to_bf16(r[0]) | (f32_to_bf16(r[1]) << 16), f32_to_bf16(r[2]) | (f32_to_bf16(r[3]) << 16)}, brs,
             oh, 0, 0);
       }
+  }
+
+  // Translated steps: the state of the blocks that are off moves to the new
+  // slot (zeros where the shifted site leaves the frame) and their activation
+  // output is refreshed; active blocks are written by their tiles. The image
+  // rows' 4-channel pieces are dealt out over the grid in strips of kMove
+  // pieces per thread, whose loads are in flight together.
+  static constexpr int kMove = 4;
+  __device__ void move_state() const {
+    const int cg = p.c_out >> 2, per_row = p.w_out * cg;
+    const int strips = (per_row + kThreads * kMove - 1) / (kThreads * kMove);
+    const int rows = p.n * p.h_out;
+    for (int it = blockIdx.x; it < rows * strips; it += gridDim.x) {
+      const int row = it / strips, strip = it - row * strips;
+      const int n = row / p.h_out, oy = row - n * p.h_out, sy = oy - p.zdy;
+      const auto srs = frame_rsrc(p.zsrc + (size_t)n * zimg, (uint32_t)(zimg * 4));
+      const auto zrs = frame_rsrc(p.z + (size_t)n * zimg, (uint32_t)(zimg * 4));
+      const auto yrs = frame_rsrc(p.act ? static_cast<uint16_t*>(p.y) + (size_t)n * zimg : nullptr,
+                                  p.act ? (uint32_t)(zimg * 2) : 0u);
+      const uint8_t* flags = p.block_mask + ((size_t)n * p.hb + (oy >> lb)) * p.wb;
+      u32x4 v[kMove];
+      uint32_t dst[kMove];
+#pragma unroll
+      for (int u = 0; u < kMove; ++u) {
+        const int e = (strip * kMove + u) * kThreads + threadIdx.x;
+        const int ox = min(e, per_row - 1) / cg, sx = ox - p.zdx;
+        const bool off = e < per_row && flags[ox >> lb] == 0;
+        dst[u] = off ? (uint32_t)((oy * per_row + e) * 16) : kOutOfRange;
+        v[u] = __builtin_amdgcn_raw_buffer_load_b128(
+            srs, off && sy >= 0 && sy < p.h_out && sx >= 0 && sx < p.w_out
+                     ? (uint32_t)((sy * per_row + e - p.zdx * cg) * 16) : kOutOfRange, 0, 0);
+      }
+#pragma unroll
+      for (int u = 0; u < kMove; ++u) {
+        __builtin_amdgcn_raw_buffer_store_b128(v[u], zrs, dst[u], 0, 0);
+        if (p.act) {
+          uint32_t q[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) q[j] = f32_to_bf16(activate(__uint_as_float(v[u][j]), p.act));
+          __builtin_amdgcn_raw_buffer_store_b64(u32x2v{q[0] | (q[1] << 16), q[2] | (q[3] << 16)}, yrs,
+                                                dst[u] == kOutOfRange ? kOutOfRange : dst[u] / 2, 0, 0);
+        }
+      }
+    }
   }
 
   // z (and the activation output) of the tile's sites

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "sc_lines.h"
+
 namespace sc {
 
 // counters[] slots in the workspace
@@ -80,6 +82,7 @@ struct ConvParams {
   int no_prev;                  // x_{t-1} taken as 0 (reference frames; residual inputs)
   int act;                      // 0 none, 1 identity, 2 relu
   int sy, sx;                   // translation of the content since x_{t-1} (input pixels; 0 = none)
+  ExposedLines ey, ex;          // output rows and columns recomputed by a translated step (else none)
   uint32_t* zero_ctr;           // work-list counters (kSegs, kSegStride apart) to clear for the next step, or NULL
   int seg_tiles, seg_cap;       // segmented work list: gate tiles and entries per tile; 0: plain list
   // residual emission in the block-halo kernel's epilogue (HaloParams::emit):
@@ -88,9 +91,11 @@ struct ConvParams {
   uint16_t* rb;
   // translated steps (block-halo convolution): z_{t-1} is read from zsrc at
   // the output site shifted back by (zdy, zdx), zero outside the frame, and
-  // the sum written to z; NULL = read z itself
+  // the sum written to z; NULL = read z itself. The kernel then also moves the
+  // state of the blocks that are off (block_mask, skipped where set).
   const float* zsrc;
   int zdy, zdx;
+  const uint8_t* block_mask;
 };
 
 // Work list of a convolution: a plain list with its count at
@@ -150,19 +155,13 @@ __device__ __forceinline__ long prev_off(const P& p, int n, int y, int x, int ch
   return ((long)(n * p.h + yp) * p.w + xq) * p.c + ch;
 }
 
-// Output line i (row or column) is "exposed" under a translation d of the
-// input (a multiple of the stride s) when its source line i - d/s is outside
-// the output grid, or when a tap p = i*s - pad + kh leaves the frame while
-// p - d lies inside it: convolution and translation do not commute there.
-__device__ __forceinline__ bool line_exposed(int i, int n_out, int n_in, int k, int s, int pad, int d) {
-  if (d == 0) return false;
-  const int src = i - d / s;
-  if (src < 0 || src >= n_out) return true;
-  for (int kh = 0; kh < k; ++kh) {
-    const int q = i * s - pad + kh;
-    if (q - d >= 0 && q - d < n_in && (q < 0 || q >= n_in)) return true;
-  }
-  return false;
+// Does the output block (bi, bj) hold an exposed line? (sc_lines.h; the ranges
+// are empty on other than translated steps.) Its sites are then computed from
+// x_t alone and assigned, like those of a reference frame.
+template <typename P>
+__device__ __forceinline__ bool block_exposed(const P& p, int bi, int bj) {
+  const int y0 = bi * p.block, x0 = bj * p.block;
+  return y0 < p.ey.lo || min(y0 + p.block, p.h_out) > p.ey.hi || x0 < p.ex.lo || min(x0 + p.block, p.w_out) > p.ex.hi;
 }
 
 // Block-halo variant of the dense bf16 convolution (see sc_conv.hip).
@@ -269,15 +268,9 @@ hipError_t launch_emit(const uint8_t* block_mask, uint8_t* prev_mask, int nb, co
                        float* r32, uint16_t* rb, int n, int hb, int wb, int block, int h_out, int w_out,
                        int c_out, int act, int dtype, int clear_only, hipStream_t st);
 
-// Translation-compensated steps (Sec. 3.3): the translated state, and the
-// active list split into translated-recurrence blocks and exposed blocks.
+// Translation-compensated steps (Sec. 3.3): the translated state.
 hipError_t launch_translate_state(const float* z_src, float* z_dst, void* y, int n, int h_out, int w_out,
-                                  int c_out, int dyo, int dxo, int act, int dtype, const uint8_t* skip_mask,
-                                  int block, int hb, int wb, hipStream_t st);
-hipError_t launch_split_list(const uint32_t* list, const uint32_t* counters, int seg_tiles, int seg_cap,
-                             uint32_t* list_a, uint32_t* counters_a, uint32_t* list_b, uint32_t* counters_b,
-                             int hb, int wb, int block, int h_out, int w_out, int h, int w, int k, int stride,
-                             int pad, int sy, int sx, hipStream_t st);
+                                  int c_out, int dyo, int dxo, int act, int dtype, hipStream_t st);
 
 hipError_t launch_fill_u32(uint32_t* p, int n, uint32_t v, hipStream_t st);
 

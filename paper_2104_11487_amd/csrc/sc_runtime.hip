@@ -64,7 +64,7 @@ struct Geometry {
   int vec;              // gate load width (elements)
   size_t elem;
   size_t off_wpack, off_slot0, off_slot1, off_z, off_y, off_bmask, off_tflag, off_list, off_ctr,
-      off_stat, off_smask, off_phi, off_r32, off_rb, off_prev, off_z2, off_list_a, off_list_b, off_wlist, off_wctr,
+      off_stat, off_smask, off_phi, off_r32, off_rb, off_prev, off_z2, off_wlist, off_wctr,
       off_ftiles, total;
   int learned;          // learned gate: its kernel size (the layer's k), else 0
   bool phi_in_lds;      // learned gate: phi staged in LDS (else read through the caches)
@@ -521,14 +521,8 @@ int derive(const skipconv_desc* d, Geometry* g, char* err) {
     G.off_prev = off;
     off = align_up(off + (size_t)nb + 16);
   }
-  G.off_z2 = G.off_list_a = G.off_list_b = off;
-  if (d->flags & SKIPCONV_FLAG_TRANSLATE) {  // second z slot and the two block lists
-    off = align_up(off + G.z_bytes);
-    G.off_list_a = off;
-    off = align_up(off + (size_t)nb * 4);
-    G.off_list_b = off;
-    off = align_up(off + (size_t)nb * 4);
-  }
+  G.off_z2 = off;
+  if (d->flags & SKIPCONV_FLAG_TRANSLATE) off = align_up(off + G.z_bytes);  // second z slot
   G.total = off;
   return SKIPCONV_OK;
 }
@@ -748,6 +742,8 @@ sc::ConvParams conv_geometry(const skipconv_desc& d, const Geometry& g, bool ref
   cp.ksteps = g.ksteps; cp.ntiles_n = g.ntn;
   cp.reference = ref ? 1 : 0;
   cp.no_prev = ref ? 1 : 0;
+  cp.ey = sc::ExposedLines{0, g.h_out};
+  cp.ex = sc::ExposedLines{0, g.w_out};
   cp.act = ((d.flags & SKIPCONV_FLAG_EMIT_RESIDUAL) && !conv_emits(g)) ? 0 : d.act_out;
   return cp;
 }
@@ -1058,19 +1054,12 @@ int skipconv_step(skipconv_t h, const void* x_t, void* stream, const float** z_t
 
   sc::GateParams gp = gate_params(h, x_t, ref);
 
-  sc::ConvParams cp{};
+  sc::ConvParams cp = conv_geometry(d, g, ref);
   cp.x_t = x_t;
   cp.x_prev = h->prev_input(x_t);
   cp.wpack = h->wpack();
   cp.z = h->z();
   cp.y = h->y();
-  cp.n = d.n; cp.h = d.h; cp.w = d.w; cp.c = d.c_in; cp.c_out = d.c_out;
-  cp.h_out = g.h_out; cp.w_out = g.w_out; cp.k = d.kernel; cp.stride = d.stride; cp.pad = g.pad;
-  cp.block = d.block; cp.hb = g.hb; cp.wb = g.wb;
-  cp.ksteps = g.ksteps; cp.ntiles_n = g.ntn;
-  cp.reference = ref ? 1 : 0;
-  cp.no_prev = ref ? 1 : 0;
-  cp.act = (h->emits() && !conv_emits(g)) ? 0 : d.act_out;
   cp.r32 = h->r32();
   cp.rb = h->rb();
 
@@ -1159,18 +1148,18 @@ int skipconv_step_translated(skipconv_t h, const void* x_t, int32_t dy, int32_t 
     if (z_t) *z_t = h->z();
     return SKIPCONV_OK;
   }
-  // 1. z <- T~(z) into the other slot (activation output refreshed). The
+  // z <- T~(z) into the other slot (activation output refreshed). The
   // block-halo convolution reads z_{t-1} from the old slot at the shifted site
-  // itself, so there the shift runs after the gate and skips active blocks.
+  // and moves the state of the blocks that are off itself.
   const float* z_old = h->z();
   const bool zshift = g.halo && !g.depthwise;
   hipError_t e = hipSuccess;
   if (!zshift)
     e = sc::launch_translate_state(z_old, h->z_other(), h->y(), d.n, g.h_out, g.w_out, d.c_out, dy / d.stride,
-                                   dx / d.stride, d.act_out, d.dtype, nullptr, d.block, g.hb, g.wb, st);
+                                   dx / d.stride, d.act_out, d.dtype, st);
   if (e != hipSuccess) return hip_fail(h, e, "translate launch");
   h->zslot ^= 1;
-  // 2. gate on r = x_t - T(x_{t-1}); exposed sites on
+  // gate on r = x_t - T(x_{t-1}); exposed sites on
   sc::GateParams gp = gate_params(h, x_t, false);
   gp.sy = dy;
   gp.sx = dx;
@@ -1178,42 +1167,34 @@ int skipconv_step_translated(skipconv_t h, const void* x_t, int32_t dy, int32_t 
   e = begin_list(h, gp, st, &sl);
   if (e == hipSuccess) e = sc::launch_gate(gp, d.dtype, g.vec, g.gate_grid, g.gate_lds, st);
   if (e == hipSuccess) e = gate_done(h, st);
-  if (e == hipSuccess && zshift)
-    e = sc::launch_translate_state(z_old, h->z(), h->y(), d.n, g.h_out, g.w_out, d.c_out, dy / d.stride,
-                                   dx / d.stride, d.act_out, d.dtype, h->bmask(), d.block, g.hb, g.wb, st);
-  // 3. active blocks: translated recurrence (list a) or recomputed from x_t (list b)
-  uint32_t* ctr = h->ctr();
-  uint32_t* list_a = reinterpret_cast<uint32_t*>(h->ws + g.off_list_a);
-  uint32_t* list_b = reinterpret_cast<uint32_t*>(h->ws + g.off_list_b);
-  if (e == hipSuccess)
-    e = sc::launch_split_list(sl.list, sl.counters, sl.seg_tiles, sl.seg_cap, list_a, ctr + 2, list_b, ctr + 3, g.hb,
-                              g.wb, d.block, g.h_out,
-                              g.w_out, d.h, d.w, d.kernel, d.stride, g.pad, dy, dx, st);
   if (e != hipSuccess) return hip_fail(h, e, "translated gate launch");
-  sc::ConvParams cp{};
+  // active blocks: the translated recurrence, or computed from x_t where exposed
+  sc::ConvParams cp = conv_geometry(d, g, false);
   cp.x_t = x_t;
   cp.x_prev = h->prev_input(x_t);
   cp.wpack = h->wpack();
   cp.z = h->z();
   cp.y = h->y();
-  cp.n = d.n; cp.h = d.h; cp.w = d.w; cp.c = d.c_in; cp.c_out = d.c_out;
-  cp.h_out = g.h_out; cp.w_out = g.w_out; cp.k = d.kernel; cp.stride = d.stride; cp.pad = g.pad;
-  cp.block = d.block; cp.hb = g.hb; cp.wb = g.wb;
-  cp.ksteps = g.ksteps; cp.ntiles_n = g.ntn;
-  cp.act = d.act_out;
-  for (int pass = 0; pass < 2 && e == hipSuccess; ++pass) {
-    cp.list = pass ? list_b : list_a;
-    cp.counters = ctr + 2 + pass;
-    cp.zero_ctr = pass ? nullptr : sl.zero;
-    cp.reference = pass;  // exposed blocks: assigned from x_t
-    cp.no_prev = pass;
-    cp.sy = pass ? 0 : dy;
-    cp.sx = pass ? 0 : dx;
-    cp.zsrc = (zshift && !pass) ? z_old : nullptr;
+  cp.list = sl.list;
+  cp.counters = sl.counters;
+  cp.zero_ctr = sl.zero;
+  cp.seg_tiles = sl.seg_tiles;
+  cp.seg_cap = sl.seg_cap;
+  cp.sy = dy;
+  cp.sx = dx;
+  cp.ey = sc::exposed_lines(g.h_out, d.h, d.kernel, d.stride, g.pad, dy);
+  cp.ex = sc::exposed_lines(g.w_out, d.w, d.kernel, d.stride, g.pad, dx);
+  int grid = conv_grid(h);
+  if (zshift) {
+    cp.zsrc = z_old;
     cp.zdy = dy / d.stride;
     cp.zdx = dx / d.stride;
-    e = launch_split_conv(g, d, cp, conv_grid(h), st);
+    cp.block_mask = h->bmask();
+    // the state of the blocks that are off is moved by the whole grid: one
+    // round of resident workgroups at least, unless the rows are fewer
+    grid = std::max(grid, std::min(h->num_cu * h->conv_occ, d.n * g.h_out));
   }
+  e = launch_split_conv(g, d, cp, grid, st);
   if (e != hipSuccess) return hip_fail(h, e, "translated conv launch");
   end_list(h);
   h->advance_input(x_t);
@@ -1278,7 +1259,7 @@ int skipconv_step_chained(skipconv_t h, skipconv_t up, void* stream, const float
   if (e == hipSuccess) e = gate_done(h, st);
   if (e != hipSuccess) return hip_fail(h, e, "chained gate launch");
   // convolution of the residual operand (bf16-rounded for bf16 layers), accumulated into z
-  sc::ConvParams cp{};
+  sc::ConvParams cp = conv_geometry(d, g, false);
   cp.x_t = bf16 ? (const void*)up->rb() : (const void*)up->r32();
   cp.x_prev = nullptr;
   cp.wpack = h->wpack();
@@ -1289,13 +1270,7 @@ int skipconv_step_chained(skipconv_t h, skipconv_t up, void* stream, const float
   cp.zero_ctr = sl.zero;
   cp.seg_tiles = sl.seg_tiles;
   cp.seg_cap = sl.seg_cap;
-  cp.n = d.n; cp.h = d.h; cp.w = d.w; cp.c = d.c_in; cp.c_out = d.c_out;
-  cp.h_out = g.h_out; cp.w_out = g.w_out; cp.k = d.kernel; cp.stride = d.stride; cp.pad = g.pad;
-  cp.block = d.block; cp.hb = g.hb; cp.wb = g.wb;
-  cp.ksteps = g.ksteps; cp.ntiles_n = g.ntn;
-  cp.reference = 0;
   cp.no_prev = 1;
-  cp.act = (h->emits() && !conv_emits(g)) ? 0 : d.act_out;
   cp.r32 = h->r32();
   cp.rb = h->rb();
   e = launch_split_conv(g, d, cp, conv_grid(h), st);
