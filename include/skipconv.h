@@ -195,6 +195,9 @@ int skipconv_create(const skipconv_desc* d, const void* weights, void* workspace
  *          x_{t-1} update, unordered work list of active blocks), then the
  *          sparse convolution kernel, which walks only the listed blocks
  *          (residual halo in LDS, MFMA product, z accumulate).
+ *   tile:  one kernel per frame on larger tiles (skipconv_pipeline: 6); also
+ *          the reference frames and translated steps of split layers it is
+ *          built for.
  * fused is chosen for shapes it is built for whose frames have at most four
  * tiles per compute unit (the variant with weights staged in LDS only for
  * layers of <= 64 input and output channels on at most one tile per compute
@@ -302,7 +305,12 @@ int skipconv_get_desc(skipconv_t h, skipconv_desc* d);
  * taps, channels split over up to 8 workgroups per tile), 5 for the
  * single-pass kernel for few input channels (fp32 C_in <= 16 or bf16
  * C_in < 8, C_out <= 64, blocks of <= 8: element halo loads, MFMA product
- * with the residual operand gathered per k index). Host only. */
+ * with the residual operand gathered per k index), 6 for the one-launch tile
+ * kernel (mid-size frames of bf16 layers with 32, 64 or 128 input channels and
+ * blocks of 1, 2, 4, 8 or 16: gate of a tile of 8 x 16 or 16 x 16 sites and the
+ * product of its active blocks in one workgroup). Reference frames and
+ * translated steps of such layers take that kernel also where this reports 0.
+ * Host only. */
 int skipconv_pipeline(skipconv_t h, int32_t* fused);
 
 /* Gate tiling of the split pipeline: *ts = output sites per side of one gate
@@ -338,8 +346,10 @@ int skipconv_copy_active_list(skipconv_t h, void* stream, uint32_t* host, size_t
  * (split pipeline): the gate kernel's work list, whose order is that of the
  * appends (unordered; every active block once), or, for blocks larger than a
  * gate tile, the ordered list the compaction wrote. capacity in entries;
- * *count receives the length. E_UNSUPPORTED after a one-pass step (it keeps
- * no list: its block flags, skipconv_copy_block_mask, are its own output). */
+ * *count receives the length. After a step of the one-launch tile kernel: the
+ * blocks whose flags its tiles set, ascending (it convolves those).
+ * E_UNSUPPORTED after a one-pass step of the other kernels (they keep no list:
+ * their block flags, skipconv_copy_block_mask, are their own output). */
 int skipconv_copy_work_list(skipconv_t h, void* stream, uint32_t* host, size_t capacity,
                             int64_t* count);
 

@@ -47,10 +47,13 @@ __device__ __forceinline__ float activate(float v, int act) { return act == 2 ? 
 
 struct HaloTile {
   int n, oy0, ox0, rows_ok, cols_ok, iy0, ix0;
-  bool fresh;  // computed from x_t alone and assigned: reference frames, exposed blocks
+  // computed from x_t alone and assigned (reference frames, exposed blocks); an
+  // int: with a bool in the struct its copies go through scratch memory
+  uint32_t fresh;
+  uint32_t live;  // MASK: bit i: this lane's site of M-tile i is updated
 };
 
-template <int WAVES_M, int WAVES_N, int WM, int WN, int KR, int KU, int ADB, bool TRANS>
+template <int WAVES_M, int WAVES_N, int WM, int WN, int KR, int KU, int ADB, bool TRANS, bool MASK = false>
 struct HaloConv {
   static constexpr int kThreads = 64 * WAVES_M * WAVES_N;
   static constexpr int kR = KR ? KR : (WN <= 2 ? 8 : (WN == 3 ? 6 : 4));  // even
@@ -60,6 +63,7 @@ struct HaloConv {
   const HaloParams& hp;
   uint8_t* halo;
   int lane, wm, r16, kq, lb, wn0, boff, chunks_per_px, csteps, total;
+  float inv_cpp, inv_hw;  // reciprocals of chunks_per_px and the halo width (qdiv)
   size_t ximg, zimg;
   __amdgpu_buffer_rsrc_t wrs;
   int abase[WM];  // halo byte offset of this lane's A row in each of its M-tiles, before the tap
@@ -71,7 +75,7 @@ struct HaloConv {
     const int wn = wave / WAVES_M;
     r16 = lane & 15;
     kq = lane >> 4;
-    lb = __ffs(p.block) - 1;
+    lb = __ffs(hp.side) - 1;
     // packed weights: lane offset in a VGPR, the (k-step, column tile) offset in an SGPR
     wrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.wpack), 0, p.ksteps * p.ntiles_n * 1024, 0x00020000);
     boff = lane * 16;
@@ -80,11 +84,13 @@ struct HaloConv {
     csteps = p.c >> 5;  // k-steps per tap
     ximg = (size_t)p.h * p.w * p.c;
     zimg = (size_t)p.h_out * p.w_out * p.c_out;
-    total = hp.hh * hp.hw * chunks_per_px;
+    total = hp.hh * hp.hw * chunks_per_px;  // < 2^20: the halo fits in LDS
+    inv_cpp = 1.0f / (float)chunks_per_px;
+    inv_hw = 1.0f / (float)hp.hw;
 #pragma unroll
     for (int i = 0; i < WM; ++i) {
       const int m = (wm * WM + i) * 16 + r16;
-      const int ly = m >> lb, lx = m & (p.block - 1);
+      const int ly = m >> lb, lx = m & (hp.side - 1);
       abase[i] = (ly * p.stride * hp.hw + lx * p.stride) * hp.pstride + kq * 16;
     }
   }
@@ -92,14 +98,22 @@ struct HaloConv {
   __device__ HaloTile tile(int n, int oy0, int ox0, bool fresh) const {
     HaloTile T;
     T.fresh = fresh;
+    T.live = ~0u;
     T.n = n;
     T.oy0 = oy0;
     T.ox0 = ox0;
     T.rows_ok = min(hp.tr, p.h_out - oy0);
-    T.cols_ok = min(p.block, p.w_out - ox0);
+    T.cols_ok = min(hp.side, p.w_out - ox0);
     T.iy0 = oy0 * p.stride - p.pad;
     T.ix0 = ox0 * p.stride - p.pad;
     return T;
+  }
+
+  // is the site (ly, lx) of this lane's M-tile i updated? MASK: the caller sets
+  // T.live per lane; otherwise every site of the tile that lies in the frame
+  __device__ bool site_ok(const HaloTile& T, int i, int ly, int lx) const {
+    if constexpr (MASK) return (T.live >> i) & 1u;
+    else return ly < T.rows_ok && lx < T.cols_ok;
   }
 
   // z byte offset (within image T.n) of this lane's piece (M-tile i, column
@@ -108,9 +122,9 @@ struct HaloConv {
     int l16 = r16;  // opaque: recomputed per use rather than held per (i, jn)
     asm volatile("" : "+v"(l16));
     const int m = (wm * WM + i) * 16 + l16;
-    const int ly = m >> lb, lx = m & (p.block - 1);
+    const int ly = m >> lb, lx = m & (hp.side - 1);
     const int col = (wn0 + jn) * 16 + kq * 4;
-    return (ly < T.rows_ok && lx < T.cols_ok && col < p.c_out)
+    return (site_ok(T, i, ly, lx) && col < p.c_out)
                ? (uint32_t)((((T.oy0 + ly) * p.w_out + T.ox0 + lx) * p.c_out + col) * 4)
                : kOutOfRange;
   }
@@ -141,10 +155,10 @@ struct HaloConv {
     int l16 = r16;
     asm volatile("" : "+v"(l16));
     const int m = (wm * WM + i) * 16 + l16;
-    const int ly = m >> lb, lx = m & (p.block - 1);
+    const int ly = m >> lb, lx = m & (hp.side - 1);
     const int col = (wn0 + jn) * 16 + kq * 4;
     const int sy = T.oy0 + ly - p.zdy, sx = T.ox0 + lx - p.zdx;
-    return (ly < T.rows_ok && lx < T.cols_ok && col < p.c_out && sy >= 0 && sy < p.h_out && sx >= 0 &&
+    return (site_ok(T, i, ly, lx) && col < p.c_out && sy >= 0 && sy < p.h_out && sx >= 0 &&
             sx < p.w_out)
                ? (uint32_t)(((sy * p.w_out + sx) * p.c_out + col) * 4)
                : kOutOfRange;
@@ -167,8 +181,8 @@ struct HaloConv {
 #pragma unroll
     for (int u = 0; u < KU; ++u) {
       const int idx = base + u * kThreads + tid;
-      const int px = idx / chunks_per_px, ch = idx - px * chunks_per_px;
-      const int hy = px / hp.hw, hx = px - hy * hp.hw;
+      const int px = qdiv(idx, inv_cpp), ch = idx - px * chunks_per_px;
+      const int hy = qdiv(px, inv_hw), hx = px - hy * hp.hw;
       const int y = T.iy0 + hy, x = T.ix0 + hx;
       const bool in = idx < total && y >= 0 && y < p.h && x >= 0 && x < p.w;
       const uint32_t off = in ? (uint32_t)(((y * p.w + x) * c + ch * 8) * 2) : kOutOfRange;
@@ -185,7 +199,7 @@ struct HaloConv {
     for (int u = 0; u < KU; ++u) {
       const int idx = base + u * kThreads + tid;
       if (idx >= total) continue;
-      const int px = idx / chunks_per_px, ch = idx - px * chunks_per_px;
+      const int px = qdiv(idx, inv_cpp), ch = idx - px * chunks_per_px;
       uint32_t q[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -208,16 +222,27 @@ struct HaloConv {
   // no data-dependent branches, so the waits count outstanding loads instead
   // of draining them; scheduling barriers keep the compiler from sinking the
   // reads back to their use.
-  __device__ void product(Acc& acc) const {
-    const int ksteps = p.ksteps, ntn = p.ntiles_n, k = p.k;
-    bf16x8 bq[kR][WN];
-    bf16x8 aq[ADB][WM];
-    auto load_b = [&](bf16x8* dst, int ks) {
+  typedef bf16x8 Ring[kR][WN];
+  __device__ void load_b(bf16x8* dst, int ks) const {
 #pragma unroll
-      for (int jn = 0; jn < WN; ++jn)
-        dst[jn] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
-                                                 wrs, boff, (ks * ntn + wn0 + jn) * 1024, 0));
-    };
+    for (int jn = 0; jn < WN; ++jn)
+      dst[jn] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
+                                               wrs, boff, (ks * p.ntiles_n + wn0 + jn) * 1024, 0));
+  }
+  // the first kR - 1 k-steps of B; they depend on nothing, so a kernel may
+  // issue them long before its halo is there
+  __device__ void start_b(Ring& bq) const {
+#pragma unroll
+    for (int r = 0; r < kR - 1; ++r) load_b(bq[r], min(r, p.ksteps - 1));
+  }
+  __device__ void product(Acc& acc) const {
+    Ring bq;
+    start_b(bq);
+    product(acc, bq);
+  }
+  __device__ void product(Acc& acc, Ring& bq) const {
+    const int ksteps = p.ksteps, k = p.k;
+    bf16x8 aq[ADB][WM];
     int aoff = 0, cc = 0, kw = 0, snext = 0;  // halo offset of the next A step (kh, kw, cc)
     // advance aoff to the following step without branches; stays on the last step
     auto advance = [&]() {
@@ -257,8 +282,6 @@ struct HaloConv {
       }
       advance();
     };
-#pragma unroll
-    for (int r = 0; r < kR - 1; ++r) load_b(bq[r], min(r, ksteps - 1));
     read_a(aq[0]);
     int ks = 0;
     for (; ks + kR <= ksteps; ks += kR) {

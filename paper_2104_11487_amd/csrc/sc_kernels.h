@@ -169,12 +169,21 @@ struct HaloParams {
   int config;            // wave layout / tile shape instantiation
   int tr;                // output rows per tile (tile = tr x block sites)
   int tiles_per_block;   // block / tr
-  int hh, hw;            // halo rows and columns: (tr-1)*s+k, (block-1)*s+k
+  int side;              // columns of a tile: the block, or the one-launch tile's width
+  int hh, hw;            // halo rows and columns: (tr-1)*s+k, (side-1)*s+k
   int pstride;           // LDS bytes per halo pixel: 2*c_in + 16
   int lds_bytes;         // hh * hw * pstride
   int threads;           // workgroup size
   int emit;              // the epilogue also writes the successor's residual (bf16, C_out % 8 == 0)
+  int rows;              // one-launch tile kernel: output rows of a tile
+  int lg_group;          // one-launch tile kernel: log2 of the lanes that hold a pixel's chunks
 };
+
+// One-launch tile kernel (sc_tile.hip): is there a build for tiles of rows x 16
+// sites and this many 16-column output tiles; its resident workgroups per CU
+// (create time: also sets the LDS attribute; 0 on error); and the launch.
+bool tile_has_build(int rows, int ntiles_n);
+int tile_occupancy(const HaloParams& hp, int ntiles_n);
 
 // Fused single-pass step for dense bf16 layers (see sc_fused.hip). `g` carries
 // the gate geometry of the fused tiling (ts, tiles, staging rows).
@@ -253,6 +262,7 @@ hipError_t launch_compact(uint8_t* block_mask, int nb, uint32_t* list, uint32_t*
                           int tiles_x, hipStream_t st);
 hipError_t launch_conv(const ConvParams& p, int dtype, bool fast, int grid, hipStream_t st);
 hipError_t launch_conv_halo(const ConvParams& p, const HaloParams& hp, int grid, hipStream_t st);
+hipError_t launch_tile(const GateParams& g, const ConvParams& c, const HaloParams& hp, hipStream_t st);
 int conv_halo_occupancy(const HaloParams& hp);  // resident workgroups per CU (0 on error)
 hipError_t launch_depthwise(const ConvParams& p, int dtype, int grid, hipStream_t st);
 // Depthwise over active blocks with the residual halo in LDS (bf16, C % 8 == 0):

@@ -23,6 +23,9 @@ constexpr size_t kLdsLimit = 60 * 1024;  // dynamic; the gate kernel adds 2 KB s
 constexpr int kMaxCout = 256;
 constexpr long kHaloLdsLimit = 160 * 1024;  // LDS of one gfx950 CU
 constexpr long kFusedLdsLimit = 156 * 1024; // dynamic LDS of the fused kernel (+ ~3 KB static)
+// dynamic LDS of the tile kernel (+ 1 KB static): three workgroups in a CU's 160 KB
+// (one with 80 KB, 64 channels at stride 2: 40.9 against 24.4 us for the 8 x 8-tile kernel)
+constexpr long kTileLdsLimit = 51 * 1024;
 constexpr long kCuGuess = 256;              // CUs assumed when a tiling is chosen before the device is queried
 
 // Does every tile's halo contain the input pixels the tile owns?
@@ -53,6 +56,10 @@ struct Geometry {
   sc::HaloParams hp;
   bool dw_halo;         // depthwise bf16: residual halo of tr x b sites in LDS
   sc::HaloParams dwp;
+  bool tile;            // one-launch tile kernel: reference frames and translated steps
+  bool tile_plain;      // ... and plain steps
+  sc::HaloParams tp;
+  int t_tiles_y, t_tiles_x;
   bool fused;           // single-pass kernel instead of gate + compaction + conv
   int f_ts, f_tiles_y, f_tiles_x, f_grid, f_copy_in_halo;
   int f_nsplit;         // workgroups per tile of the register-operand kernel (output channels split)
@@ -309,6 +316,7 @@ int derive(const skipconv_desc* d, Geometry* g, char* err) {
     H.emit = (d->flags & SKIPCONV_FLAG_EMIT_RESIDUAL) && d->c_out % 8 == 0 ? 1 : 0;
     H.tiles_per_block = b / H.tr;
     H.hh = (H.tr - 1) * s + k;
+    H.side = b;
     H.hw = (b - 1) * s + k;
     H.pstride = 2 * d->c_in + 16;
     const long lds = (long)H.hh * H.hw * H.pstride;
@@ -317,6 +325,45 @@ int derive(const skipconv_desc* d, Geometry* g, char* err) {
       G.halo = true;
       G.conv_max_tiles = G.nb * H.tiles_per_block;
     }
+  }
+
+  // one-launch tile kernel (norm gates, no emission, whole pixels in a lane
+  // group): tiles of 16 x 16 or, for blocks of at most 8, 8 x 16 sites (128
+  // input channels: 8 x 16 only, by the halo's size)
+  G.tile = G.tile_plain = false;
+  if (!depthwise && d->dtype == SKIPCONV_BF16 && (d->c_in == 32 || d->c_in == 64 || d->c_in == 128) &&
+      d->c_out % 4 == 0 && (b & (b - 1)) == 0 && b <= 16 && !G.learned &&
+      !(d->flags & (SKIPCONV_FLAG_SPLIT_PIPELINE | SKIPCONV_FLAG_EMIT_RESIDUAL | SKIPCONV_FLAG_LARGE_GATE_TILES)) &&
+      (long)d->h * d->w * d->c_in * 4 < (1L << 31) && (long)G.h_out * G.w_out * d->c_out * 4 < (1L << 31)) {
+    sc::HaloParams& H = G.tp;
+    H.pstride = 2 * d->c_in + 16;
+    H.lg_group = d->c_in == 32 ? 2 : (d->c_in == 64 ? 3 : 4);
+    H.side = 16;
+    H.hw = (H.side - 1) * s + k;
+    // 16 rows read 1.27 x the tile's pixels (8 rows: 1.41 x) but give half the
+    // workgroups: 8 rows while 16 x 16 tiles would be fewer than two per CU
+    // (one 256 x 256 x 64 frame, translated: 20.3 against 22.6 us; four
+    // 512 x 512 x 32 frames, reference: 110 against 91 us)
+    const long tiles16 = (long)d->n * ((G.h_out + 15) / 16) * ((G.w_out + 15) / 16);
+    const int first = b <= 8 && tiles16 < 2 * kCuGuess ? 8 : 16;
+    for (int rows = first; rows >= 8; rows -= 8) {
+      H.rows = H.tr = rows;
+      H.hh = (rows - 1) * s + k;
+      const long lds = (long)H.hh * H.hw * H.pstride;
+      if (b > rows || !sc::tile_has_build(rows, G.ntn) || lds + (long)H.hh * H.hw * 4 > kTileLdsLimit) continue;
+      H.lds_bytes = (int)lds;
+      G.t_tiles_y = (G.h_out + rows - 1) / rows;
+      G.t_tiles_x = (G.w_out + H.side - 1) / H.side;
+      G.tile = halo_covers_owned(d->h, G.h_out, rows, G.t_tiles_y, s, pad, k) &&
+               halo_covers_owned(d->w, G.w_out, H.side, G.t_tiles_x, s, pad, k);
+      break;
+    }
+    // plain steps: few tiles per CU, where two kernels are mostly latency, and
+    // blocks smaller than 8, whose other convolution gathers site by site.
+    // Measured (tile / split, us): 64 -> 64, 16 x 16 blocks, 2 x 256 x 256
+    // 26.4 / 30.1, 512 x 512 42 / 40.7; per-site gates 4 x 512 x 512 140 / 172;
+    // 128 channels on either side 2 x 256 x 256 33.5 / 30.6 and 55 / 46.
+    G.tile_plain = G.tile && d->c_in <= 64 && (G.ntn == 2 || G.ntn == 4) && (tiles16 <= 2 * kCuGuess || b < 8);
   }
 
   // fused single-pass kernel: dense bf16, C_in % 32 == 0, tiles of <= 16 x 16
@@ -584,7 +631,8 @@ struct skipconv_layer {
   int wslot = 0;
   bool wclean[2] = {true, true};
   // the list the last step's convolution walked: 0 none (one-pass kernel),
-  // 1 the ordered list, 2 the segmented work list of slot work_slot
+  // 1 the ordered list, 2 the segmented work list of slot work_slot, 3 none:
+  // the tile kernel convolves the blocks whose flags it sets
   int work_kind = 0, work_slot = 0;
   uint32_t* wlist() { return reinterpret_cast<uint32_t*>(ws + g.off_wlist); }
   uint32_t* wctr() { return reinterpret_cast<uint32_t*>(ws + g.off_wctr); }
@@ -849,6 +897,15 @@ void end_list(skipconv_layer* h) {
   h->wslot ^= 1;
 }
 
+// A plain or translated step as one launch of the tile kernel.
+hipError_t launch_tile(skipconv_layer* h, sc::GateParams gp, const sc::ConvParams& cp, hipStream_t st) {
+  gp.tiles_y = h->g.t_tiles_y;
+  gp.tiles_x = h->g.t_tiles_x;
+  h->list_valid = false;
+  h->work_kind = 3;
+  return sc::launch_tile(gp, cp, h->g.tp, st);
+}
+
 int conv_grid(const skipconv_layer* h) { return conv_grid_of(h->g, h->num_cu, h->conv_occ); }
 
 // ---- scratch of skipconv_step_static ----
@@ -992,6 +1049,23 @@ int skipconv_create(const skipconv_desc* d, const void* weights, void* workspace
     const long cap = (long)(d->c_in * d->c_out <= 32 * 32 ? 3 : 1) * h->num_cu;
     if (d->c_in > 64 || d->c_out > 64 || h->g.f_grid > cap) h->g.fused = false;
   }
+  // The one-launch tile kernel takes over from the 8 x 8-tile kernels once
+  // their workgroups come in more than two rounds (64 -> 64, one 180 x 180
+  // frame: 17.2 -> 15.4 us; 256 x 256: 23.7 -> 17.7 us), or more than one where
+  // K is short or the output wide (160 x 160: 32 -> 32 9.4 -> 7.8 us, 64 -> 128
+  // 17.0 -> 14.2 us); before that they win (64 -> 64, 160 x 160: 12.8 against
+  // 13.4 us, 128 x 96: 7.0 against 12 us; 1 x 1 128 -> 64, 136 x 136: 10.6
+  // against 12.8 us).
+  if (h->g.tile && sc::tile_occupancy(h->g.tp, h->g.ntn) < 1) h->g.tile = h->g.tile_plain = false;
+  if (h->g.fused) {
+    const long wgs = (long)h->g.f_grid * h->g.f_nsplit;
+    if (h->g.tile && h->g.f_mw == 1 && wgs > (d->c_in <= 64 && (h->g.ksteps <= 9 || h->g.ntn >= 8) ? 1 : 2) * (long)h->num_cu) {
+      h->g.fused = false;
+      h->g.tile_plain = true;
+    } else {
+      h->g.tile = h->g.tile_plain = false;
+    }
+  }
   h->conv_occ = conv_setup(h->g, d, h->device);
   if (workspace) {
     h->ws = static_cast<char*>(workspace);
@@ -1069,7 +1143,11 @@ int skipconv_step(skipconv_t h, const void* x_t, void* stream, const float** z_t
 
   hipError_t e = hipSuccess;
   if (timing) e = hipEventRecord(h->ev[3 * h->timing_done], st);
-  if (g.fused) {
+  if (g.tile_plain || (g.tile && ref)) {
+    if (e == hipSuccess) e = launch_tile(h, gp, cp, st);
+    if (e != hipSuccess) return hip_fail(h, e, "tile launch");
+    if (timing) e = hipEventRecord(h->ev[3 * h->timing_done + 1], st);
+  } else if (g.fused) {
     const sc::FusedParams fp = fused_params(h, x_t, ref);
     if (e == hipSuccess) e = sc::launch_fused(fp, g.f_grid * fp.nsplit, st);
     if (e != hipSuccess) return hip_fail(h, e, "fused launch");
@@ -1152,7 +1230,7 @@ int skipconv_step_translated(skipconv_t h, const void* x_t, int32_t dy, int32_t 
   // block-halo convolution reads z_{t-1} from the old slot at the shifted site
   // and moves the state of the blocks that are off itself.
   const float* z_old = h->z();
-  const bool zshift = g.halo && !g.depthwise;
+  const bool zshift = g.tile || (g.halo && !g.depthwise);
   hipError_t e = hipSuccess;
   if (!zshift)
     e = sc::launch_translate_state(z_old, h->z_other(), h->y(), d.n, g.h_out, g.w_out, d.c_out, dy / d.stride,
@@ -1163,11 +1241,6 @@ int skipconv_step_translated(skipconv_t h, const void* x_t, int32_t dy, int32_t 
   sc::GateParams gp = gate_params(h, x_t, false);
   gp.sy = dy;
   gp.sx = dx;
-  StepList sl{};
-  e = begin_list(h, gp, st, &sl);
-  if (e == hipSuccess) e = sc::launch_gate(gp, d.dtype, g.vec, g.gate_grid, g.gate_lds, st);
-  if (e == hipSuccess) e = gate_done(h, st);
-  if (e != hipSuccess) return hip_fail(h, e, "translated gate launch");
   // active blocks: the translated recurrence, or computed from x_t where exposed
   sc::ConvParams cp = conv_geometry(d, g, false);
   cp.x_t = x_t;
@@ -1175,28 +1248,37 @@ int skipconv_step_translated(skipconv_t h, const void* x_t, int32_t dy, int32_t 
   cp.wpack = h->wpack();
   cp.z = h->z();
   cp.y = h->y();
-  cp.list = sl.list;
-  cp.counters = sl.counters;
-  cp.zero_ctr = sl.zero;
-  cp.seg_tiles = sl.seg_tiles;
-  cp.seg_cap = sl.seg_cap;
   cp.sy = dy;
   cp.sx = dx;
   cp.ey = sc::exposed_lines(g.h_out, d.h, d.kernel, d.stride, g.pad, dy);
   cp.ex = sc::exposed_lines(g.w_out, d.w, d.kernel, d.stride, g.pad, dx);
-  int grid = conv_grid(h);
   if (zshift) {
     cp.zsrc = z_old;
     cp.zdy = dy / d.stride;
     cp.zdx = dx / d.stride;
     cp.block_mask = h->bmask();
+  }
+  if (g.tile) {
+    e = launch_tile(h, gp, cp, st);
+    if (e != hipSuccess) return hip_fail(h, e, "translated tile launch");
+  } else {
+    StepList sl{};
+    e = begin_list(h, gp, st, &sl);
+    if (e == hipSuccess) e = sc::launch_gate(gp, d.dtype, g.vec, g.gate_grid, g.gate_lds, st);
+    if (e == hipSuccess) e = gate_done(h, st);
+    if (e != hipSuccess) return hip_fail(h, e, "translated gate launch");
+    cp.list = sl.list;
+    cp.counters = sl.counters;
+    cp.zero_ctr = sl.zero;
+    cp.seg_tiles = sl.seg_tiles;
+    cp.seg_cap = sl.seg_cap;
     // the state of the blocks that are off is moved by the whole grid: one
     // round of resident workgroups at least, unless the rows are fewer
-    grid = std::max(grid, std::min(h->num_cu * h->conv_occ, d.n * g.h_out));
+    const int grid = zshift ? std::max(conv_grid(h), std::min(h->num_cu * h->conv_occ, d.n * g.h_out)) : conv_grid(h);
+    e = launch_split_conv(g, d, cp, grid, st);
+    if (e != hipSuccess) return hip_fail(h, e, "translated conv launch");
+    end_list(h);
   }
-  e = launch_split_conv(g, d, cp, grid, st);
-  if (e != hipSuccess) return hip_fail(h, e, "translated conv launch");
-  end_list(h);
   h->advance_input(x_t);
   h->ref_pending = false;
   ++h->frames;
@@ -1331,7 +1413,7 @@ int skipconv_activation(skipconv_t h, const void** y) {
 int skipconv_pipeline(skipconv_t h, int32_t* fused) {
   if (!h) return SKIPCONV_E_STATE;
   if (!fused) return SKIPCONV_E_INVALID_ARG;
-  *fused = h->g.fused ? (h->g.f_sc ? 5 : (h->g.f_dw ? 4 : (h->g.f_rb ? (h->g.f_nsplit > 1 ? 3 : 2) : 1))) : 0;
+  *fused = h->g.tile_plain ? 6 : h->g.fused ? (h->g.f_sc ? 5 : (h->g.f_dw ? 4 : (h->g.f_rb ? (h->g.f_nsplit > 1 ? 3 : 2) : 1))) : 0;
   return SKIPCONV_OK;
 }
 
@@ -1430,6 +1512,18 @@ int skipconv_copy_work_list(skipconv_t h, void* stream, uint32_t* host, size_t c
   if (h->frames == 0) return fail(h->last_error, SKIPCONV_E_STATE, "no step yet");
   if (h->work_kind == 0)
     return fail(h->last_error, SKIPCONV_E_UNSUPPORTED, "one-pass kernel: no work list (its block flags are the block mask)");
+  if (h->work_kind == 3) {  // the tile kernel's own list: the blocks whose flags it set
+    std::vector<uint8_t> m(h->g.nb);
+    const int rc = copy_back(h, stream, m.data(), h->bmask(), m.size());
+    if (rc) return rc;
+    *count = 0;
+    for (int i = 0; i < h->g.nb; ++i) {
+      if (!m[i]) continue;
+      if ((size_t)*count < capacity) host[*count] = (uint32_t)i;
+      ++*count;
+    }
+    return (size_t)*count > capacity ? fail(h->last_error, SKIPCONV_E_SMALL_BUFFER, "list buffer too small") : SKIPCONV_OK;
+  }
   if (h->work_kind == 1) {  // the ordered list the compaction wrote for the convolution
     uint32_t cnt = 0;
     int rc = copy_back(h, stream, &cnt, h->ctr() + sc::kCtrCount, 4);

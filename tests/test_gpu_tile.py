@@ -1,0 +1,78 @@
+"""One-launch tile kernel (reference frames, translated steps, plain steps of mid-size frames)
+against the CPU oracle: masks, statistics and counts bit for bit, z within the accumulation-order
+bound, activation output bit for bit, on ragged frames at the edges of its tiles and shapes."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import skipconv_oracle as O  # noqa: E402
+from paper_2104_11487_amd import synthetic as syn  # noqa: E402
+from parity_util import compare_frame, eps_for_density, say, to_device  # noqa: E402
+from test_gpu_parity import _layer_pair, oracle_stats  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+# (n, h, w, c_in, c_out, k, stride, block, pipeline reported): tiles of 8 and
+# 16 rows, every column build, ragged last tiles, partial output columns,
+# k = 1 and 5, stride 2; 0 where only reference frames and translated steps
+# take the kernel
+CASES = [
+    (1, 181, 187, 64, 64, 3, 1, 8, 6), (1, 181, 187, 32, 20, 3, 1, 1, 6), (2, 130, 141, 32, 64, 1, 1, 2, 6),
+    (1, 150, 140, 64, 128, 3, 1, 4, 6), (1, 100, 91, 128, 128, 3, 1, 8, 6), (3, 170, 171, 64, 64, 3, 1, 16, 6),
+    (1, 41, 70, 64, 12, 3, 1, 16, 0), (1, 37, 50, 64, 8, 3, 1, 4, 0), (1, 183, 185, 32, 32, 5, 1, 8, 6),
+    (1, 281, 290, 32, 48, 3, 2, 4, 6), (9, 160, 240, 32, 40, 3, 1, 8, 0), (5, 250, 243, 32, 100, 1, 1, 16, 0),
+]
+
+
+@pytest.mark.parametrize("caller", [False, True], ids=["copy", "retains"])
+@pytest.mark.parametrize("case", CASES, ids=["x".join(map(str, c)) for c in CASES])
+def test_tile_kernel(case, caller):
+    n, h, w, ci, co, k, s, b, kind = case
+    if caller and n * h * w > 20000:
+        pytest.skip("the frame contract is covered on the smaller frames")
+    rng = np.random.Generator(np.random.PCG64(40 + ci + co + k + b))
+    vid = syn.RectVideo(h, w, ci, 5, seed=41 + ci + b, batch=n, n_rect=3, side_lo=9, side_hi=30)
+    base = list(vid)
+    shifts = [(0, 0), (0, 0), (s, -2 * s), (0, 0), (-s, 0)]
+    frames, acc = [], (0, 0)
+    for f, d in zip(base, shifts):
+        acc = (acc[0] + d[0], acc[1] + d[1])
+        frames.append(O.translate(f, *acc))
+    wt = rng.normal(0, 0.15, (co, ci, k, k)).astype(np.float32)
+    pad = (k - 1) // 2
+    ho, wo = O.out_size(h, k, s, pad), O.out_size(w, k, s, pad)
+    eps = eps_for_density(oracle_stats(base[:2], wt.shape, dtype="bf16", stride=s), b, ho, wo, 0.3)
+    big = n * h * w > 100000
+    layer, orc = _layer_pair(wt, n=n, h=h, w=w, dtype="bf16", eps=eps, block=b, stride=s, translate=True,
+                             act_out="relu", caller_retains=caller, keep_stats=not big)
+    assert layer.fused_variant == kind, (case, layer.fused_variant)
+    for t, (f, d) in enumerate(zip(frames[:3] if big else frames, shifts)):
+        if t == 3:
+            layer.reset()
+            orc.reset()
+        xs = syn.to_storage(f, "bf16")
+        say(f"[tile {case}] frame {t} shift={d} eps={eps:.4g}")
+        layer.step_translated(to_device(xs, "bf16"), *d)
+        ref = orc.step(xs, shift=d)
+        compare_frame(layer, ref, "bf16", t=t, tag=f"tile {case}", keep_stats=not big)
+        z = layer._z.cpu().numpy()
+        y = layer.activation().view(torch.int16).cpu().numpy().view(np.uint16).reshape(z.shape)
+        assert np.array_equal(y, O.f32_to_bf16_rne(np.maximum(z, 0.0).astype(np.float32))), (case, t)
+    layer.close()
+
+
+def test_tile_kernel_integer_frames_are_the_dense_convolution():
+    """eps = 0 on integer frames and weights: every sum is exact, so z is conv2d(x_t) bit for bit."""
+    rng = np.random.Generator(np.random.PCG64(5))
+    wt = rng.integers(-2, 3, (64, 64, 3, 3)).astype(np.float32)
+    layer, orc = _layer_pair(wt, n=1, h=185, w=184, dtype="bf16", eps=0.0, block=8, keep_stats=False)
+    assert layer.fused_variant == 6
+    x = rng.integers(0, 4, (1, 185, 184, 64)).astype(np.float32)
+    for t in range(3):
+        x = x.copy()
+        x[:, 20 * t:20 * t + 50, 30:90] = rng.integers(0, 4, (1, 50, 60, 64))
+        xs = syn.to_storage(x, "bf16")
+        layer.step(to_device(xs, "bf16"))
+        compare_frame(layer, orc.step(xs), "bf16", t=t, tag="tile integer", keep_stats=False, exact_z=True)
+    layer.close()
