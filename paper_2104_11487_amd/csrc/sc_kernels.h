@@ -183,6 +183,8 @@ struct HaloParams {
 // sites and this many 16-column output tiles; its resident workgroups per CU
 // (create time: also sets the LDS attribute; 0 on error); and the launch.
 bool tile_has_build(int rows, int ntiles_n);
+// does its learned gate hold this tile's halo (kernel size `learned`, c channels)?
+bool tile_learned_fits(const HaloParams& hp, int ntiles_n, int c, int learned);
 int tile_occupancy(const HaloParams& hp, int ntiles_n);
 
 // Fused single-pass step for dense bf16 layers (see sc_fused.hip). `g` carries

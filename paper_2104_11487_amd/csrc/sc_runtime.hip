@@ -332,7 +332,7 @@ int derive(const skipconv_desc* d, Geometry* g, char* err) {
   // input channels: 8 x 16 only, by the halo's size)
   G.tile = G.tile_plain = false;
   if (!depthwise && d->dtype == SKIPCONV_BF16 && (d->c_in == 32 || d->c_in == 64 || d->c_in == 128) &&
-      d->c_out % 4 == 0 && (b & (b - 1)) == 0 && b <= 16 && !G.learned &&
+      d->c_out % 4 == 0 && (b & (b - 1)) == 0 && b <= 16 &&
       !(d->flags & (SKIPCONV_FLAG_SPLIT_PIPELINE | SKIPCONV_FLAG_EMIT_RESIDUAL | SKIPCONV_FLAG_LARGE_GATE_TILES)) &&
       (long)d->h * d->w * d->c_in * 4 < (1L << 31) && (long)G.h_out * G.w_out * d->c_out * 4 < (1L << 31)) {
     sc::HaloParams& H = G.tp;
@@ -351,6 +351,7 @@ int derive(const skipconv_desc* d, Geometry* g, char* err) {
       H.hh = (rows - 1) * s + k;
       const long lds = (long)H.hh * H.hw * H.pstride;
       if (b > rows || !sc::tile_has_build(rows, G.ntn) || lds + (long)H.hh * H.hw * 4 > kTileLdsLimit) continue;
+      if (G.learned && !sc::tile_learned_fits(H, G.ntn, d->c_in, G.learned)) continue;
       H.lds_bytes = (int)lds;
       G.t_tiles_y = (G.h_out + rows - 1) / rows;
       G.t_tiles_x = (G.w_out + H.side - 1) / H.side;
@@ -363,7 +364,9 @@ int derive(const skipconv_desc* d, Geometry* g, char* err) {
     // Measured (tile / split, us): 64 -> 64, 16 x 16 blocks, 2 x 256 x 256
     // 26.4 / 30.1, 512 x 512 42 / 40.7; per-site gates 4 x 512 x 512 140 / 172;
     // 128 channels on either side 2 x 256 x 256 33.5 / 30.6 and 55 / 46.
-    G.tile_plain = G.tile && d->c_in <= 64 && (G.ntn == 2 || G.ntn == 4) && (tiles16 <= 2 * kCuGuess || b < 8);
+    // The learned gate is VALU work, so its tiles gain at every size.
+    G.tile_plain = G.tile && (G.learned || (d->c_in <= 64 && (G.ntn == 2 || G.ntn == 4) &&
+                                            (tiles16 <= 2 * kCuGuess || b < 8)));
   }
 
   // fused single-pass kernel: dense bf16, C_in % 32 == 0, tiles of <= 16 x 16
@@ -1230,7 +1233,8 @@ int skipconv_step_translated(skipconv_t h, const void* x_t, int32_t dy, int32_t 
   // block-halo convolution reads z_{t-1} from the old slot at the shifted site
   // and moves the state of the blocks that are off itself.
   const float* z_old = h->z();
-  const bool zshift = g.tile || (g.halo && !g.depthwise);
+  const bool tile = g.tile && !g.learned;
+  const bool zshift = tile || (g.halo && !g.depthwise);
   hipError_t e = hipSuccess;
   if (!zshift)
     e = sc::launch_translate_state(z_old, h->z_other(), h->y(), d.n, g.h_out, g.w_out, d.c_out, dy / d.stride,
@@ -1258,7 +1262,7 @@ int skipconv_step_translated(skipconv_t h, const void* x_t, int32_t dy, int32_t 
     cp.zdx = dx / d.stride;
     cp.block_mask = h->bmask();
   }
-  if (g.tile) {
+  if (tile) {
     e = launch_tile(h, gp, cp, st);
     if (e != hipSuccess) return hip_fail(h, e, "translated tile launch");
   } else {

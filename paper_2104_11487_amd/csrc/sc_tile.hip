@@ -51,10 +51,11 @@ __device__ __forceinline__ float group_sum_lg(float v, int lg) {
 // OCC: waves per SIMD the register budget aims for. ZI: the accumulators start
 // from z_{t-1}; otherwise it is added after the product (one rounding of the
 // update on the state, as in the kernels this one takes over from).
-template <int WAVES_M, int WAVES_N, int WM, int WN, int KR, int OCC, int KI, bool ZI, bool TRANS>
+template <int WAVES_M, int WAVES_N, int WM, int WN, int KR, int OCC, int KI, bool ZI, bool TRANS, int LEARN>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) __attribute__((amdgpu_waves_per_eu(OCC)))
 tile_kernel(GateParams g, ConvParams c, HaloParams hp) {
   constexpr int kTileThreads = 64 * WAVES_M * WAVES_N;
+  static_assert(!LEARN || !TRANS, "learned gates take the split pipeline for translated steps");
   typedef HaloConv<WAVES_M, WAVES_N, WM, WN, KR, 1, 1, TRANS, true> HC;
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   __shared__ uint32_t blk_flag[kMaxTileBlocks];
@@ -76,7 +77,7 @@ tile_kernel(GateParams g, ConvParams c, HaloParams hp) {
 
   HC H(c, hp, lds);
   typename HC::Ring bq;
-  H.start_b(bq);
+  if constexpr (!LEARN) H.start_b(bq);
   if (threadIdx.x < kMaxTileBlocks) blk_flag[threadIdx.x] = 0u;
 
   // ---- halo ----
@@ -149,14 +150,148 @@ tile_kernel(GateParams g, ConvParams c, HaloParams hp) {
       }
     }
   };
-  halo(std::true_type{});
-  lds_barrier();
-
-  // ---- gate: support statistic, threshold, block flags ----
   const int tb_w = tw >> lblk;
-  {
-    const int ly = threadIdx.x >> lw, lx = threadIdx.x & (tw - 1);  // one site per thread
-    if (ly < oh && lx < ow) {
+  // the gate of one site: statistic or score sv
+  auto decide = [&](int ly, int lx, float sv, bool above) {
+    const int oy = oy0 + ly, ox = ox0 + lx;
+    bool on = g.reference || g.force_dense || above || (sv != sv);
+    if constexpr (TRANS) on = on || oy < c.ey.lo || oy >= c.ey.hi || ox < c.ex.lo || ox >= c.ex.hi;
+    if (g.keep_stats) {
+      const size_t o = ((size_t)n * g.h_out + oy) * g.w_out + ox;
+      g.stat[o] = sv;
+      g.site_mask[o] = on ? 1 : 0;
+    }
+    if (on) blk_flag[(ly >> lblk) * tb_w + (lx >> lblk)] = 1u;
+  };
+  const int ly = (threadIdx.x >> lw) & (th - 1), lx = threadIdx.x & (tw - 1);  // this thread's site
+  if constexpr (LEARN) {
+    // ---- learned gate (Eq. 8): one thread per site and share of the taps ----
+    // A score takes 2 k^2 C_in rounded operations a site in a fixed order, so
+    // the work is VALU issue: every (site, tap) pair is formed once, by the
+    // thread of that site (the halo pixels' terms of every tap, formed per
+    // pixel and exchanged through LDS, took 1.56 x the products on 8 x 8 tiles
+    // and most of their time in the exchange). phi comes through the scalar
+    // cache, two 8-channel chunks of the residual at a time through LDS (20
+    // floats a pixel: 16 sites of a row read distinct banks), and the frames'
+    // chunks stay in registers, from which an active tile then writes rho.
+    constexpr int K2 = LEARN * LEARN, kSites = 16 * WM * WAVES_M, kSplit = kTileThreads / kSites;
+    constexpr int TPT = (K2 + kSplit - 1) / kSplit;  // taps per thread
+    constexpr int RS = 20;                           // floats of a pixel in the residual buffer
+    float* rbuf = reinterpret_cast<float*>(lds);
+    u32x4 vt[KI], vp[KI];
+    const int ch = threadIdx.x & (group - 1);  // the same for every item of the thread
+    auto each = [&](auto body) {
+#pragma unroll
+      for (int u = 0; u < KI; ++u) {
+        int tid = threadIdx.x;  // opaque: recomputed, not held
+        asm volatile("" : "+v"(tid));
+        const int idx = u * kTileThreads + tid;
+        body(u, idx >> lg, idx < total);
+      }
+    };
+    each([&](int u, int q, bool valid) {
+      const int hy = qdiv(q, inv_hw), hx = q - hy * hw;
+      const int y = iy0 + hy, x = ix0 + hx;
+      const bool in = valid && y >= 0 && y < g.h && x >= 0 && x < g.w;
+      const uint32_t off = in ? (uint32_t)(((y * g.w + x) * g.c + ch * kChunk) * 2) : kOutOfRange;
+      vt[u] = __builtin_amdgcn_raw_buffer_load_b128(rt, off, 0, 0);
+      vp[u] = __builtin_amdgcn_raw_buffer_load_b128(rp, g.no_prev ? kOutOfRange : off, 0, 0);
+    });
+    auto residual = [&](int u, float (&r)[kChunk]) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t a = vt[u][e], b = vp[u][e];
+        r[2 * e] = __fsub_rn(__uint_as_float(a << 16), __uint_as_float(b << 16));
+        r[2 * e + 1] = __fsub_rn(__uint_as_float(a & 0xffff0000u), __uint_as_float(b & 0xffff0000u));
+      }
+    };
+    float acc[TPT];
+#pragma unroll
+    for (int i = 0; i < TPT; ++i) acc[i] = 0.0f;
+    const int tg = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kSites);  // share of the taps (whole waves)
+    const bool score = !g.reference || g.keep_stats;
+    typedef const __attribute__((address_space(4))) float const_f32;
+    const const_f32* phi = (const const_f32*)g.phi;
+    const int nchk = g.c >> 3;
+    for (int c0 = 0; c0 < nchk && score; c0 += 2) {
+      if ((ch >> 1) == (c0 >> 1))
+        each([&](int u, int q, bool valid) {
+          float r[kChunk];
+          residual(u, r);
+          float4* d = reinterpret_cast<float4*>(rbuf + q * RS + (ch & 1) * kChunk);
+          if (valid) {
+            d[0] = make_float4(r[0], r[1], r[2], r[3]);
+            d[1] = make_float4(r[4], r[5], r[6], r[7]);
+          }
+        });
+      lds_barrier();
+#pragma unroll
+      for (int i = 0; i < TPT; ++i) {
+        const int t = tg * TPT + i, kh = t / LEARN, kw = t - kh * LEARN;  // uniform
+        if (t < K2) {
+          const float4* rr = reinterpret_cast<const float4*>(rbuf + ((ly * s + kh) * hw + lx * s + kw) * RS);
+#pragma unroll
+          for (int cc = 0; cc < 2; ++cc) {
+            const const_f32* ph = phi + t * g.c + (c0 + cc) * kChunk;
+            const float4 a = rr[2 * cc], b = rr[2 * cc + 1];
+            const float r[kChunk] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+            // (the chunk sum's own first addition to +0 is left out: a sum of
+            // -0 terms becomes +0 in the next one)
+            float part = mul_rn(ph[0], r[0]);
+#pragma unroll
+            for (int j = 1; j < kChunk; ++j) part = add_rn(part, mul_rn(ph[j], r[j]));
+            acc[i] = add_rn(acc[i], part);
+          }
+        }
+      }
+      lds_barrier();  // the next chunks overwrite the buffer
+    }
+    // the owned pixels' state copy, past the loads that the scores waited for
+    each([&](int u, int q, bool valid) {
+      const int hy = qdiv(q, inv_hw), hx = q - hy * hw;
+      const int y = iy0 + hy, x = ix0 + hx;
+      const bool own = valid && keep_on && y >= own_y0 && y < own_y1 && x >= own_x0 && x < own_x1;
+      __builtin_amdgcn_raw_buffer_store_b128(
+          vt[u], rk, own ? (uint32_t)(((y * g.w + x) * g.c + ch * kChunk) * 2) : kOutOfRange, 0, kNonTemporal);
+    });
+    // the taps' sums of a site meet in tap order (an out-of-frame tap's sum is
+    // +0, which adds nothing), then the bias
+    if constexpr (kSplit > 1) {
+      if (tg > 0) {
+#pragma unroll
+        for (int i = 0; i < TPT; ++i)
+          if (tg * TPT + i < K2) rbuf[(tg * TPT + i) * kSites + (threadIdx.x & (kSites - 1))] = acc[i];
+      }
+      lds_barrier();
+    }
+    if (threadIdx.x < kSites && ly < oh && lx < ow) {
+      float sv = 0.0f;
+#pragma unroll
+      for (int t = 0; t < K2; ++t) sv = add_rn(sv, t < TPT ? acc[t < TPT ? t : 0] : rbuf[t * kSites + threadIdx.x]);
+      sv = add_rn(sv, g.gate_bias);
+      decide(ly, lx, sv, sv > 0.0f);
+    }
+    lds_barrier();
+    // an active tile writes rho and fetches its first weights; the others end
+    uint32_t any = 0u;
+    for (int i = threadIdx.x & 63; i < (th >> lblk) * tb_w; i += 64) any |= blk_flag[i];
+    const bool active = __ballot(any != 0u) != 0ull;  // every wave sees all flags: uniform
+    if (active) {
+      H.start_b(bq);
+      each([&](int u, int q, bool valid) {
+        float r[kChunk];
+        residual(u, r);
+        if (valid)
+          *reinterpret_cast<u32x4*>(lds + q * hp.pstride + ch * 16) =
+              u32x4{pack_bf16(r[0], r[1]), pack_bf16(r[2], r[3]), pack_bf16(r[4], r[5]), pack_bf16(r[6], r[7])};
+      });
+    }
+  } else {
+    halo(std::true_type{});
+    lds_barrier();
+
+    // ---- gate: support statistic, threshold, block flags ----
+    if (threadIdx.x < th * tw && ly < oh && lx < ow) {
       float sv = 0.0f;
       if (g.support == 0) {
         const float* base = a_halo + (ly * s) * hw + lx * s;
@@ -165,15 +300,7 @@ tile_kernel(GateParams g, ConvParams c, HaloParams hp) {
       } else {
         sv = a_halo[(ly * s + g.pad) * hw + lx * s + g.pad];
       }
-      const int oy = oy0 + ly, ox = ox0 + lx;
-      bool on = g.reference || g.force_dense || ((double)sv * g.wnorm > g.thr) || (sv != sv);
-      if constexpr (TRANS) on = on || oy < c.ey.lo || oy >= c.ey.hi || ox < c.ex.lo || ox >= c.ex.hi;
-      if (g.keep_stats) {
-        const size_t o = ((size_t)n * g.h_out + oy) * g.w_out + ox;
-        g.stat[o] = sv;
-        g.site_mask[o] = on ? 1 : 0;
-      }
-      if (on) blk_flag[(ly >> lblk) * tb_w + (lx >> lblk)] = 1u;
+      decide(ly, lx, sv, (double)sv * g.wnorm > g.thr);
     }
   }
   lds_barrier();
@@ -281,12 +408,17 @@ tile_kernel(GateParams g, ConvParams c, HaloParams hp) {
 using TileKernel = void (*)(GateParams, ConvParams, HaloParams);
 struct TileBuild {
   int rows, ntn, threads;
-  TileKernel plain, trans;
+  TileKernel plain, trans, learned1, learned3;
 };
+// learned gate: halo chunks per thread, all in registers: (rows + 2) x 18
+// pixels of up to 64 channels
+constexpr int kLearnItems(int rows, int waves) { return ((rows + 2) * 18 * 8 + waves * 64 - 1) / (waves * 64); }
 const TileBuild kTileBuilds[] = {
 #define SC_X(rows, ntn, a, b, wm, wn, kr, zi, krt, occ, ki)                          \
-  {rows, ntn, 64 * a * b, tile_kernel<a, b, wm, wn, kr, occ, ki, zi, false>, \
-   tile_kernel<a, b, wm, wn, krt, occ, ki, true, true>},
+  {rows, ntn, 64 * a * b, tile_kernel<a, b, wm, wn, kr, occ, ki, zi, false, 0>,      \
+   tile_kernel<a, b, wm, wn, krt, occ, ki, true, true, 0>,                           \
+   tile_kernel<a, b, wm, wn, kr, occ, kLearnItems(rows, a * b), zi, false, 1>,       \
+   tile_kernel<a, b, wm, wn, kr, occ, kLearnItems(rows, a * b), zi, false, 3>},
     SC_TILE_BUILDS(SC_X)
 #undef SC_X
 };
@@ -303,11 +435,17 @@ int tile_lds(const HaloParams& hp) { return hp.lds_bytes + (hp.hh * hp.hw * 4 + 
 
 bool tile_has_build(int rows, int ntiles_n) { return tile_build(rows, ntiles_n) != nullptr; }
 
+bool tile_learned_fits(const HaloParams& hp, int ntiles_n, int c, int learned) {
+  const TileBuild* b = tile_build(hp.rows, ntiles_n);
+  return b && c <= 64 && (learned == 1 || learned == 3) &&
+         (hp.hh * hp.hw) << hp.lg_group <= kLearnItems(hp.rows, b->threads / 64) * b->threads;
+}
+
 int tile_occupancy(const HaloParams& hp, int ntiles_n) {
   const TileBuild* b = tile_build(hp.rows, ntiles_n);
   int blocks = 0;
   if (!b) return 0;
-  for (TileKernel f : {b->trans, b->plain})
+  for (TileKernel f : {b->learned1, b->learned3, b->trans, b->plain})
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize,
                             tile_lds(hp)) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, f, b->threads, tile_lds(hp)) != hipSuccess)
@@ -318,7 +456,8 @@ int tile_occupancy(const HaloParams& hp, int ntiles_n) {
 hipError_t launch_tile(const GateParams& g, const ConvParams& c, const HaloParams& hp, hipStream_t st) {
   const TileBuild* b = tile_build(hp.rows, c.ntiles_n);
   if (!b) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(c.zsrc ? b->trans : b->plain, dim3(g.n * g.tiles_y * g.tiles_x), dim3(b->threads), tile_lds(hp),
+  const TileKernel f = c.zsrc ? b->trans : (g.learned == 1 ? b->learned1 : (g.learned == 3 ? b->learned3 : b->plain));
+  hipLaunchKernelGGL(f, dim3(g.n * g.tiles_y * g.tiles_x), dim3(b->threads), tile_lds(hp),
                      st, g, c, hp);
   return hipGetLastError();
 }

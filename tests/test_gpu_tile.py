@@ -76,3 +76,35 @@ def test_tile_kernel_integer_frames_are_the_dense_convolution():
         layer.step(to_device(xs, "bf16"))
         compare_frame(layer, orc.step(xs), "bf16", t=t, tag="tile integer", keep_stats=False, exact_z=True)
     layer.close()
+
+
+# learned gate (Eq. 8) in the tile kernel: every column build, both tile
+# heights, 3 x 3 and 1 x 1 (taps shared by one, two or four thread groups)
+LEARNED = [(1, 181, 187, 64, 64, 3, 8), (1, 150, 141, 32, 20, 3, 1), (3, 170, 171, 64, 64, 3, 16), (1, 41, 70, 64, 12, 3, 16),
+           (1, 37, 50, 32, 8, 3, 4), (1, 190, 180, 64, 128, 1, 4), (2, 150, 170, 64, 100, 3, 2), (1, 190, 181, 32, 32, 1, 8)]
+
+
+@pytest.mark.parametrize("stats", [True, False], ids=["stats", "nostats"])
+@pytest.mark.parametrize("case", LEARNED, ids=["x".join(map(str, c)) for c in LEARNED])
+def test_tile_kernel_learned_gate(case, stats):
+    n, h, w, ci, co, k, b = case
+    if not stats and n * h * w > 10000:
+        pytest.skip("covered on the smaller frames")
+    rng = np.random.Generator(np.random.PCG64(70 + ci + co + k + b))
+    frames = list(syn.RectVideo(h, w, ci, 4, seed=71 + ci + b, batch=n, n_rect=3, side_lo=9, side_hi=30))
+    wt = rng.normal(0, 0.15, (co, ci, k, k)).astype(np.float32)
+    phi = rng.normal(0, 1.0 / np.sqrt(ci * k * k), (ci, k, k)).astype(np.float32)
+    layer, orc = _layer_pair(wt, n=n, h=h, w=w, dtype="bf16", eps=0.0, block=b, gate="learned", phi=phi, gate_bias=-0.25,
+                             act_out="identity", keep_stats=stats)
+    assert layer.fused_variant == 6, (case, layer.fused_variant)
+    for t, f in enumerate(frames):
+        if t == 3:
+            layer.reset()
+            orc.reset()
+        xs = syn.to_storage(f, "bf16")
+        say(f"[tile learned {case}] frame {t}")
+        layer.step(to_device(xs, "bf16"))
+        ref = orc.step(xs)
+        compare_frame(layer, ref, "bf16", t=t, tag=f"tile learned {case}", keep_stats=stats)
+        assert t == 0 or t == 3 or 0 < ref["count"] < ref["block_mask"].size, "the gate decides nothing"
+    layer.close()
