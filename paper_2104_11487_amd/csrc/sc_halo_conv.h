@@ -23,6 +23,9 @@
 // conditional and the wait counts are static.
 //
 // Waves are laid out WAVES_M x WAVES_N; each owns WM x WN 16x16 output tiles.
+// TAB (C_in % 8 == 0): the four 8-channel chunks of a k-step
+// may lie on different taps, so a table in LDS holds the halo offset of every
+// chunk of K; the chunks past K read a zero word there.
 // KR: B register ring (0 picks 8 / 6 / 4 by WN). KU: halo items (two 16-byte
 // loads each) in flight per thread. ADB: A fragment register sets (2: the next
 // step's fragments are read before this step's MFMAs; 1: M-tile by M-tile
@@ -53,7 +56,7 @@ struct HaloTile {
   uint32_t live;  // MASK: bit i: this lane's site of M-tile i is updated
 };
 
-template <int WAVES_M, int WAVES_N, int WM, int WN, int KR, int KU, int ADB, bool TRANS, bool MASK = false>
+template <int WAVES_M, int WAVES_N, int WM, int WN, int KR, int KU, int ADB, bool TRANS, bool MASK = false, bool TAB = false>
 struct HaloConv {
   static constexpr int kThreads = 64 * WAVES_M * WAVES_N;
   static constexpr int kR = KR ? KR : (WN <= 2 ? 8 : (WN == 3 ? 6 : 4));  // even
@@ -66,6 +69,8 @@ struct HaloConv {
   float inv_cpp, inv_hw;  // reciprocals of chunks_per_px and the halo width (qdiv)
   size_t ximg, zimg;
   __amdgpu_buffer_rsrc_t wrs;
+  const int* tab = nullptr;  // TAB: ksteps x 4 chunk offsets (-1 past K)
+  int zero = 0;              // TAB: halo offset of 16 zero bytes
   int abase[WM];  // halo byte offset of this lane's A row in each of its M-tiles, before the tap
 
   __device__ HaloConv(const ConvParams& p_, const HaloParams& hp_, uint8_t* halo_) : p(p_), hp(hp_), halo(halo_) {
@@ -91,8 +96,21 @@ struct HaloConv {
     for (int i = 0; i < WM; ++i) {
       const int m = (wm * WM + i) * 16 + r16;
       const int ly = m >> lb, lx = m & (hp.side - 1);
-      abase[i] = (ly * p.stride * hp.hw + lx * p.stride) * hp.pstride + kq * 16;
+      abase[i] = (ly * p.stride * hp.hw + lx * p.stride) * hp.pstride + (TAB ? 0 : kq * 16);
     }
+  }
+
+  // TAB: fill the table (and the zero word) at `t`; a barrier must follow
+  __device__ void make_tab(int* t, int threads) {
+    const int nq = p.k * p.k * chunks_per_px;
+    for (int q = threadIdx.x; q < p.ksteps * 4 + 4; q += threads) {
+      const int tap = q / chunks_per_px, ch = q - tap * chunks_per_px;
+      const int kh = tap / p.k, kw = tap - kh * p.k;
+      // the last four ints are the zero word
+      t[q] = q >= p.ksteps * 4 ? 0 : (q < nq ? (kh * hp.hw + kw) * hp.pstride + ch * 16 : -1);
+    }
+    tab = t;
+    zero = (int)(reinterpret_cast<uint8_t*>(t + p.ksteps * 4) - halo);
   }
 
   __device__ HaloTile tile(int n, int oy0, int ox0, bool fresh) const {
@@ -244,9 +262,23 @@ struct HaloConv {
     const int ksteps = p.ksteps, k = p.k;
     bf16x8 aq[ADB][WM];
     int aoff = 0, cc = 0, kw = 0, snext = 0;  // halo offset of the next A step (kh, kw, cc)
+    int anext = 0;                            // TAB: of the step after it
+    if constexpr (TAB) {
+      aoff = tab[kq];
+      anext = tab[min(1, ksteps - 1) * 4 + kq];
+    }
+    auto a_at = [&](int i) {
+      const int o = abase[i] + aoff;
+      return *reinterpret_cast<const bf16x8*>(halo + (TAB && aoff < 0 ? zero : o));
+    };
     // advance aoff to the following step without branches; stays on the last step
     auto advance = [&]() {
       const bool more = ++snext < ksteps;
+      if constexpr (TAB) {
+        aoff = anext;
+        anext = tab[min(snext + 1, ksteps - 1) * 4 + kq];
+        return;
+      }
       const int c1 = cc + 1;
       const bool wrap = c1 == csteps;
       const int kw1 = kw + (wrap ? 1 : 0);
@@ -260,7 +292,7 @@ struct HaloConv {
     };
     auto read_a = [&](bf16x8* dst) {
 #pragma unroll
-      for (int i = 0; i < WM; ++i) dst[i] = *reinterpret_cast<const bf16x8*>(halo + abase[i] + aoff);
+      for (int i = 0; i < WM; ++i) dst[i] = a_at(i);
       advance();
     };
     auto mfmas = [&](const bf16x8* a, const bf16x8* bf) {
@@ -278,7 +310,7 @@ struct HaloConv {
 #pragma unroll
         for (int jn = 0; jn < WN; ++jn)
           acc[i][jn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[jn], a[i], acc[i][jn], 0, 0, 0);
-        a[i] = *reinterpret_cast<const bf16x8*>(halo + abase[i] + aoff);
+        a[i] = a_at(i);
       }
       advance();
     };

@@ -177,15 +177,17 @@ struct HaloParams {
   int emit;              // the epilogue also writes the successor's residual (bf16, C_out % 8 == 0)
   int rows;              // one-launch tile kernel: output rows of a tile
   int lg_group;          // one-launch tile kernel: log2 of the lanes that hold a pixel's chunks
+  int tab_off;           // one-launch tile kernel: LDS offset of the chunk table (C_in not 32, 64, 128), else 0
+  int part_off;          // one-launch tile kernel: LDS offset of the chunk sums (> 16 chunks a pixel), else 0
 };
 
-// One-launch tile kernel (sc_tile.hip): is there a build for tiles of rows x 16
-// sites and this many 16-column output tiles; its resident workgroups per CU
-// (create time: also sets the LDS attribute; 0 on error); and the launch.
-bool tile_has_build(int rows, int ntiles_n);
-// does its learned gate hold this tile's halo (kernel size `learned`, c channels)?
-bool tile_learned_fits(const HaloParams& hp, int ntiles_n, int c, int learned);
-int tile_occupancy(const HaloParams& hp, int ntiles_n);
+// One-launch tile kernel (sc_tile.hip). tile_shape completes `hp` (rows, side,
+// hh and hw set by the caller: tiles of rows x side sites and their halo) for C
+// input channels; false when no build takes it within lds_limit bytes.
+// tile_occupancy: resident workgroups per CU (create time: also sets the LDS
+// attribute; 0 on error).
+bool tile_shape(HaloParams& hp, int ntiles_n, int ksteps, int c, int learned, int lds_limit);
+int tile_occupancy(const HaloParams& hp, int ntiles_n, int ksteps);
 
 // Fused single-pass step for dense bf16 layers (see sc_fused.hip). `g` carries
 // the gate geometry of the fused tiling (ts, tiles, staging rows).

@@ -327,45 +327,45 @@ int derive(const skipconv_desc* d, Geometry* g, char* err) {
     }
   }
 
-  // one-launch tile kernel (norm gates, no emission, whole pixels in a lane
-  // group): tiles of 16 x 16 or, for blocks of at most 8, 8 x 16 sites (128
-  // input channels: 8 x 16 only, by the halo's size)
+  // one-launch tile kernel (no emission, whole 8-channel chunks): tiles of 16 x
+  // 16, 8 x 16 or (C_in % 32 != 0) 8 x 8 sites
   G.tile = G.tile_plain = false;
-  if (!depthwise && d->dtype == SKIPCONV_BF16 && (d->c_in == 32 || d->c_in == 64 || d->c_in == 128) &&
-      d->c_out % 4 == 0 && (b & (b - 1)) == 0 && b <= 16 &&
+  if (!depthwise && d->dtype == SKIPCONV_BF16 && d->c_in % 8 == 0 && d->c_in >= 16 && d->c_in <= 256 &&
+      (d->c_in <= 128 || d->c_in % 32) && d->c_out % 4 == 0 && (b & (b - 1)) == 0 && b <= 16 &&
       !(d->flags & (SKIPCONV_FLAG_SPLIT_PIPELINE | SKIPCONV_FLAG_EMIT_RESIDUAL | SKIPCONV_FLAG_LARGE_GATE_TILES)) &&
       (long)d->h * d->w * d->c_in * 4 < (1L << 31) && (long)G.h_out * G.w_out * d->c_out * 4 < (1L << 31)) {
     sc::HaloParams& H = G.tp;
-    H.pstride = 2 * d->c_in + 16;
-    H.lg_group = d->c_in == 32 ? 2 : (d->c_in == 64 ? 3 : 4);
-    H.side = 16;
-    H.hw = (H.side - 1) * s + k;
     // 16 rows read 1.27 x the tile's pixels (8 rows: 1.41 x) but give half the
     // workgroups: 8 rows while 16 x 16 tiles would be fewer than two per CU
     // (one 256 x 256 x 64 frame, translated: 20.3 against 22.6 us; four
-    // 512 x 512 x 32 frames, reference: 110 against 91 us)
+    // 512 x 512 x 32 frames, reference: 110 against 91 us), and 8 x 8 sites
+    // while 8 x 16 would be fewer than one
     const long tiles16 = (long)d->n * ((G.h_out + 15) / 16) * ((G.w_out + 15) / 16);
-    const int first = b <= 8 && tiles16 < 2 * kCuGuess ? 8 : 16;
-    for (int rows = first; rows >= 8; rows -= 8) {
-      H.rows = H.tr = rows;
-      H.hh = (rows - 1) * s + k;
-      const long lds = (long)H.hh * H.hw * H.pstride;
-      if (b > rows || !sc::tile_has_build(rows, G.ntn) || lds + (long)H.hh * H.hw * 4 > kTileLdsLimit) continue;
-      if (G.learned && !sc::tile_learned_fits(H, G.ntn, d->c_in, G.learned)) continue;
-      H.lds_bytes = (int)lds;
-      G.t_tiles_y = (G.h_out + rows - 1) / rows;
+    static const int shapes[][2] = {{16, 16}, {8, 16}, {8, 8}};
+    const bool mixed = d->c_in % 32 != 0;
+    const int first = b > 8 || tiles16 >= 2 * kCuGuess ? 0 : (mixed && 2 * tiles16 < kCuGuess ? 2 : 1);
+    for (int i = first; i < 3 && !G.tile && b <= shapes[i][0]; ++i) {
+      H.rows = H.tr = shapes[i][0];
+      H.side = shapes[i][1];
+      H.hh = (H.rows - 1) * s + k;
+      H.hw = (H.side - 1) * s + k;
+      // three workgroups in a CU's LDS, or, where the other convolution gathers, what fits
+      const long limit = !mixed ? kTileLdsLimit : (i == 2 || b > 8 ? kFusedLdsLimit : 78 * 1024);
+      if (!sc::tile_shape(H, G.ntn, G.ksteps, d->c_in, G.learned, (int)limit)) continue;
+      G.t_tiles_y = (G.h_out + H.rows - 1) / H.rows;
       G.t_tiles_x = (G.w_out + H.side - 1) / H.side;
-      G.tile = halo_covers_owned(d->h, G.h_out, rows, G.t_tiles_y, s, pad, k) &&
+      G.tile = halo_covers_owned(d->h, G.h_out, H.rows, G.t_tiles_y, s, pad, k) &&
                halo_covers_owned(d->w, G.w_out, H.side, G.t_tiles_x, s, pad, k);
-      break;
+      if (!G.tile) break;
     }
     // plain steps: few tiles per CU, where two kernels are mostly latency, and
     // blocks smaller than 8, whose other convolution gathers site by site.
     // Measured (tile / split, us): 64 -> 64, 16 x 16 blocks, 2 x 256 x 256
     // 26.4 / 30.1, 512 x 512 42 / 40.7; per-site gates 4 x 512 x 512 140 / 172;
     // 128 channels on either side 2 x 256 x 256 33.5 / 30.6 and 55 / 46.
-    // The learned gate is VALU work, so its tiles gain at every size.
-    G.tile_plain = G.tile && (G.learned || (d->c_in <= 64 && (G.ntn == 2 || G.ntn == 4) &&
+    // The learned gate is VALU work, so its tiles gain at every size, and so do
+    // channel counts whose other convolution gathers site by site.
+    G.tile_plain = G.tile && (G.learned || mixed || (d->c_in <= 64 && (G.ntn == 2 || G.ntn == 4) &&
                                             (tiles16 <= 2 * kCuGuess || b < 8)));
   }
 
@@ -1059,7 +1059,7 @@ int skipconv_create(const skipconv_desc* d, const void* weights, void* workspace
   // 17.0 -> 14.2 us); before that they win (64 -> 64, 160 x 160: 12.8 against
   // 13.4 us, 128 x 96: 7.0 against 12 us; 1 x 1 128 -> 64, 136 x 136: 10.6
   // against 12.8 us).
-  if (h->g.tile && sc::tile_occupancy(h->g.tp, h->g.ntn) < 1) h->g.tile = h->g.tile_plain = false;
+  if (h->g.tile && sc::tile_occupancy(h->g.tp, h->g.ntn, h->g.ksteps) < 1) h->g.tile = h->g.tile_plain = false;
   if (h->g.fused) {
     const long wgs = (long)h->g.f_grid * h->g.f_nsplit;
     if (h->g.tile && h->g.f_mw == 1 && wgs > (d->c_in <= 64 && (h->g.ksteps <= 9 || h->g.ntn >= 8) ? 1 : 2) * (long)h->num_cu) {

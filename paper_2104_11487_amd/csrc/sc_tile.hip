@@ -51,15 +51,16 @@ __device__ __forceinline__ float group_sum_lg(float v, int lg) {
 // OCC: waves per SIMD the register budget aims for. ZI: the accumulators start
 // from z_{t-1}; otherwise it is added after the product (one rounding of the
 // update on the state, as in the kernels this one takes over from).
-template <int WAVES_M, int WAVES_N, int WM, int WN, int KR, int OCC, int KI, bool ZI, bool TRANS, int LEARN>
+template <int WAVES_M, int WAVES_N, int WM, int WN, int KR, int OCC, int KI, bool ZI, bool TRANS, int LEARN, bool TAB>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) __attribute__((amdgpu_waves_per_eu(OCC)))
 tile_kernel(GateParams g, ConvParams c, HaloParams hp) {
   constexpr int kTileThreads = 64 * WAVES_M * WAVES_N;
   static_assert(!LEARN || !TRANS, "learned gates take the split pipeline for translated steps");
-  typedef HaloConv<WAVES_M, WAVES_N, WM, WN, KR, 1, 1, TRANS, true> HC;
+  typedef HaloConv<WAVES_M, WAVES_N, WM, WN, KR, 1, 1, TRANS, true, TAB> HC;
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   __shared__ uint32_t blk_flag[kMaxTileBlocks];
   float* a_halo = reinterpret_cast<float*>(lds + hp.lds_bytes);
+  float* part = reinterpret_cast<float*>(lds + hp.part_off);
 
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
   const int per_img = g.tiles_y * g.tiles_x;
@@ -78,6 +79,7 @@ tile_kernel(GateParams g, ConvParams c, HaloParams hp) {
   HC H(c, hp, lds);
   typename HC::Ring bq;
   if constexpr (!LEARN) H.start_b(bq);
+  if constexpr (TAB) H.make_tab(reinterpret_cast<int*>(lds + hp.tab_off), kTileThreads);
   if (threadIdx.x < kMaxTileBlocks) blk_flag[threadIdx.x] = 0u;
 
   // ---- halo ----
@@ -87,7 +89,7 @@ tile_kernel(GateParams g, ConvParams c, HaloParams hp) {
   const auto rp = frame_rsrc(static_cast<const uint16_t*>(g.no_prev ? g.x_t : g.x_prev) + img, img_bytes);
   const bool keep_on = g.x_keep != nullptr;
   const auto rk = frame_rsrc(keep_on ? static_cast<uint16_t*>(g.x_keep) + img : nullptr, keep_on ? img_bytes : 0u);
-  const int lg = hp.lg_group, group = 1 << lg;
+  const int lg = hp.lg_group, group = 1 << lg, nchk = g.c >> 3;
   const int total = (hh * hw) << lg;
   const float inv_hw = 1.0f / (float)hw;
   const int wave0 = threadIdx.x & ~63;
@@ -105,7 +107,9 @@ tile_kernel(GateParams g, ConvParams c, HaloParams hp) {
         const int q = idx >> lg, ch = idx & (group - 1);
         const int hy = qdiv(q, inv_hw), hx = q - hy * hw;
         const int y = iy0 + hy, x = ix0 + hx;
-        const bool in = idx < total && y >= 0 && y < g.h && x >= 0 && x < g.w;
+        // (TAB: a group may have more lanes than the pixel has chunks; the spare
+        // ones load nothing and add +0 after the last chunk)
+        const bool in = idx < total && (!TAB || ch < nchk) && y >= 0 && y < g.h && x >= 0 && x < g.w;
         const uint32_t off = (uint32_t)(((y * g.w + x) * g.c + ch * kChunk) * 2);
         vt[u] = __builtin_amdgcn_raw_buffer_load_b128(rt, in ? off : kOutOfRange, 0, 0);
         if constexpr (kFirst) {
@@ -138,10 +142,14 @@ tile_kernel(GateParams g, ConvParams c, HaloParams hp) {
             sum = add_rn(sum, term(r1, g.norm_p));
             rho[e] = pack_bf16(r0, r1);
           }
-          const float acc = group_sum_lg(sum, lg);
-          if (idx < total && ch == 0) a_halo[q] = acc;
+          if (TAB && hp.part_off) {
+            if (idx < total && ch < nchk) part[q * (nchk | 1) + ch] = sum;
+          } else {
+            const float acc = group_sum_lg(sum, lg);
+            if (idx < total && ch == 0) a_halo[q] = acc;
+          }
         }
-        if (idx < total) *reinterpret_cast<u32x4*>(lds + q * hp.pstride + ch * 16) = rho;
+        if (idx < total && (!TAB || ch < nchk)) *reinterpret_cast<u32x4*>(lds + q * hp.pstride + ch * 16) = rho;
       }
       if constexpr (kFirst) {
 #pragma unroll
@@ -212,7 +220,6 @@ tile_kernel(GateParams g, ConvParams c, HaloParams hp) {
     const bool score = !g.reference || g.keep_stats;
     typedef const __attribute__((address_space(4))) float const_f32;
     const const_f32* phi = (const const_f32*)g.phi;
-    const int nchk = g.c >> 3;
     for (int c0 = 0; c0 < nchk && score; c0 += 2) {
       if ((ch >> 1) == (c0 >> 1))
         each([&](int u, int q, bool valid) {
@@ -289,6 +296,14 @@ tile_kernel(GateParams g, ConvParams c, HaloParams hp) {
   } else {
     halo(std::true_type{});
     lds_barrier();
+    if (TAB && hp.part_off) {  // more than 16 chunks a pixel: their sums meet in LDS
+      for (int q = threadIdx.x; q < hh * hw; q += kTileThreads) {
+        float a = 0.0f;
+        for (int i = 0; i < nchk; ++i) a = add_rn(a, part[q * (nchk | 1) + i]);
+        a_halo[q] = a;
+      }
+      lds_barrier();
+    }
 
     // ---- gate: support statistic, threshold, block flags ----
     if (threadIdx.x < th * tw && ly < oh && lx < ow) {
@@ -395,69 +410,98 @@ tile_kernel(GateParams g, ConvParams c, HaloParams hp) {
   }
 }
 
-// Builds by tile rows (16 x 16 or 8 x 16 sites) and 16-column output tiles:
-// rows, ntn, WAVES_M, WAVES_N, WM, WN, KR and ZI of plain steps, KR of
-// translated steps (which start the accumulators from z: with z held beside
-// them the 128-register builds spill), OCC, KI.
-#define SC_TILE_BUILDS(X)                                                                             \
-  X(16, 1, 4, 1, 4, 1, 4, false, 4, 3, 6) X(16, 2, 4, 2, 4, 1, 4, false, 4, 4, 3)                     \
-  X(16, 4, 4, 2, 4, 2, 2, false, 4, 4, 3) X(16, 8, 4, 2, 4, 4, 2, true, 2, 2, 3)                      \
-  X(8, 1, 4, 1, 2, 1, 4, false, 4, 4, 4) X(8, 2, 4, 1, 2, 2, 4, false, 4, 4, 4)                       \
-  X(8, 4, 2, 2, 4, 2, 2, false, 4, 4, 3) X(8, 8, 2, 4, 4, 2, 2, false, 4, 4, 3)
+// Builds by tile extent (16 x 16, 8 x 16 or 8 x 8 sites) and 16-column output
+// tiles: rows, columns, ntn, WAVES_M, WAVES_N, WM, WN, KR and ZI of plain
+// steps, KR of translated steps (which start the accumulators from z: with z
+// held beside them the 128-register builds spill), OCC, KI.
+#define SC_TILE_BUILDS(X)                                                                                 \
+  X(16, 16, 1, 4, 1, 4, 1, 4, false, 4, 3, 6) X(16, 16, 2, 4, 2, 4, 1, 4, false, 4, 4, 3)                 \
+  X(16, 16, 4, 4, 2, 4, 2, 2, false, 4, 4, 3) X(16, 16, 8, 4, 2, 4, 4, 2, true, 2, 2, 3)                  \
+  X(8, 16, 1, 4, 1, 2, 1, 4, false, 4, 4, 4) X(8, 16, 2, 4, 1, 2, 2, 4, false, 4, 4, 4)                   \
+  X(8, 16, 4, 2, 2, 4, 2, 2, false, 4, 4, 3) X(8, 16, 8, 2, 4, 4, 2, 2, false, 4, 4, 3)
+// Other than 32, 64 or 128 input channels (TAB): also 8 x 8 tiles and up to 256
+// output channels, since the only other convolution of C_in % 32 != 0 gathers
+// site by site.
+#define SC_TILE_BUILDS_TAB(X)                                                                             \
+  SC_TILE_BUILDS(X) X(8, 16, 12, 2, 4, 4, 3, 2, true, 2, 2, 3) X(8, 16, 16, 2, 4, 4, 4, 2, true, 2, 2, 3) \
+  X(8, 8, 1, 4, 1, 1, 1, 4, false, 4, 4, 4) X(8, 8, 2, 4, 1, 1, 2, 4, false, 4, 4, 4)                     \
+  X(8, 8, 4, 2, 2, 2, 2, 4, false, 4, 4, 4) X(8, 8, 8, 2, 4, 2, 2, 4, false, 4, 4, 3)                     \
+  X(8, 8, 12, 2, 4, 2, 3, 2, false, 2, 4, 3) X(8, 8, 16, 2, 4, 2, 4, 2, false, 2, 4, 3)
 
 using TileKernel = void (*)(GateParams, ConvParams, HaloParams);
 struct TileBuild {
-  int rows, ntn, threads;
+  int rows, cols, ntn, threads;
   TileKernel plain, trans, learned1, learned3;
 };
 // learned gate: halo chunks per thread, all in registers: (rows + 2) x 18
 // pixels of up to 64 channels
 constexpr int kLearnItems(int rows, int waves) { return ((rows + 2) * 18 * 8 + waves * 64 - 1) / (waves * 64); }
 const TileBuild kTileBuilds[] = {
-#define SC_X(rows, ntn, a, b, wm, wn, kr, zi, krt, occ, ki)                          \
-  {rows, ntn, 64 * a * b, tile_kernel<a, b, wm, wn, kr, occ, ki, zi, false, 0>,      \
-   tile_kernel<a, b, wm, wn, krt, occ, ki, true, true, 0>,                           \
-   tile_kernel<a, b, wm, wn, kr, occ, kLearnItems(rows, a * b), zi, false, 1>,       \
-   tile_kernel<a, b, wm, wn, kr, occ, kLearnItems(rows, a * b), zi, false, 3>},
+#define SC_X(rows, cols, ntn, a, b, wm, wn, kr, zi, krt, occ, ki)                          \
+  {rows, cols, ntn, 64 * a * b, tile_kernel<a, b, wm, wn, kr, occ, ki, zi, false, 0, false>, \
+   tile_kernel<a, b, wm, wn, krt, occ, ki, true, true, 0, false>,                            \
+   tile_kernel<a, b, wm, wn, kr, occ, kLearnItems(rows, a * b), zi, false, 1, false>,        \
+   tile_kernel<a, b, wm, wn, kr, occ, kLearnItems(rows, a * b), zi, false, 3, false>},
     SC_TILE_BUILDS(SC_X)
 #undef SC_X
 };
+const TileBuild kTabBuilds[] = {
+#define SC_X(rows, cols, ntn, a, b, wm, wn, kr, zi, krt, occ, ki)                         \
+  {rows, cols, ntn, 64 * a * b, tile_kernel<a, b, wm, wn, kr, occ, ki, zi, false, 0, true>, \
+   tile_kernel<a, b, wm, wn, krt, occ, ki, true, true, 0, true>, nullptr, nullptr},
+    SC_TILE_BUILDS_TAB(SC_X)
+#undef SC_X
+};
 
-const TileBuild* tile_build(int rows, int ntn) {
-  for (const TileBuild& b : kTileBuilds)
-    if (b.rows == rows && b.ntn == ntn) return &b;
-  return nullptr;
+const TileBuild* tile_build(const HaloParams& hp, int ntn) {
+  auto find = [&](auto& builds) -> const TileBuild* {
+    for (const TileBuild& b : builds)
+      if (b.rows == hp.rows && b.cols == hp.side && b.ntn == ntn) return &b;
+    return nullptr;
+  };
+  return hp.tab_off ? find(kTabBuilds) : find(kTileBuilds);
 }
 
-int tile_lds(const HaloParams& hp) { return hp.lds_bytes + (hp.hh * hp.hw * 4 + 15) / 16 * 16; }
+// rho halo, pixel statistics, the chunk table with its zero word, chunk sums
+int tile_lds(const HaloParams& hp, int ksteps) {
+  if (hp.part_off) return hp.part_off + hp.hh * hp.hw * (((hp.pstride - 16) / 16) | 1) * 4;
+  return hp.tab_off ? hp.tab_off + (ksteps * 4 + 4) * 4 : hp.lds_bytes + (hp.hh * hp.hw * 4 + 15) / 16 * 16;
+}
 
 }  // namespace
 
-bool tile_has_build(int rows, int ntiles_n) { return tile_build(rows, ntiles_n) != nullptr; }
-
-bool tile_learned_fits(const HaloParams& hp, int ntiles_n, int c, int learned) {
-  const TileBuild* b = tile_build(hp.rows, ntiles_n);
-  return b && c <= 64 && (learned == 1 || learned == 3) &&
-         (hp.hh * hp.hw) << hp.lg_group <= kLearnItems(hp.rows, b->threads / 64) * b->threads;
+bool tile_shape(HaloParams& hp, int ntiles_n, int ksteps, int c, int learned, int lds_limit) {
+  hp.pstride = 2 * c + 16;
+  hp.lds_bytes = hp.hh * hp.hw * hp.pstride;
+  hp.tab_off = c == 32 || c == 64 || c == 128 ? 0 : hp.lds_bytes + (hp.hh * hp.hw * 4 + 15) / 16 * 16;
+  hp.lg_group = 1;
+  while ((c >> 3) > 1 << hp.lg_group) ++hp.lg_group;
+  hp.part_off = hp.lg_group > 4 ? hp.tab_off + (ksteps * 4 + 4) * 4 : 0;
+  const TileBuild* b = tile_build(hp, ntiles_n);
+  if (!b || hp.lg_group > 5 || tile_lds(hp, ksteps) > lds_limit) return false;
+  return !learned || (!hp.tab_off && c <= 64 && (learned == 1 || learned == 3) &&
+                      (hp.hh * hp.hw) << hp.lg_group <= kLearnItems(hp.rows, b->threads / 64) * b->threads);
 }
 
-int tile_occupancy(const HaloParams& hp, int ntiles_n) {
-  const TileBuild* b = tile_build(hp.rows, ntiles_n);
+int tile_occupancy(const HaloParams& hp, int ntiles_n, int ksteps) {
+  const TileBuild* b = tile_build(hp, ntiles_n);
   int blocks = 0;
   if (!b) return 0;
+  const int lds = tile_lds(hp, ksteps);
   for (TileKernel f : {b->learned1, b->learned3, b->trans, b->plain})
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            tile_lds(hp)) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, f, b->threads, tile_lds(hp)) != hipSuccess)
+    if (f && (hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize, lds) !=
+                  hipSuccess ||
+              hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, f, b->threads, lds) != hipSuccess))
       return 0;
   return blocks;
 }
 
 hipError_t launch_tile(const GateParams& g, const ConvParams& c, const HaloParams& hp, hipStream_t st) {
-  const TileBuild* b = tile_build(hp.rows, c.ntiles_n);
+  const TileBuild* b = tile_build(hp, c.ntiles_n);
   if (!b) return hipErrorInvalidValue;
+  if (!c.zsrc && g.learned && !(g.learned == 1 ? b->learned1 : b->learned3)) return hipErrorInvalidValue;
   const TileKernel f = c.zsrc ? b->trans : (g.learned == 1 ? b->learned1 : (g.learned == 3 ? b->learned3 : b->plain));
-  hipLaunchKernelGGL(f, dim3(g.n * g.tiles_y * g.tiles_x), dim3(b->threads), tile_lds(hp),
+  hipLaunchKernelGGL(f, dim3(g.n * g.tiles_y * g.tiles_x), dim3(b->threads), tile_lds(hp, c.ksteps),
                      st, g, c, hp);
   return hipGetLastError();
 }

@@ -21,6 +21,12 @@ CASES = [
     (1, 181, 187, 64, 64, 3, 1, 8, 6), (1, 181, 187, 32, 20, 3, 1, 1, 6), (2, 130, 141, 32, 64, 1, 1, 2, 6),
     (1, 150, 140, 64, 128, 3, 1, 4, 6), (1, 100, 91, 128, 128, 3, 1, 8, 6), (3, 170, 171, 64, 64, 3, 1, 16, 6),
     (1, 41, 70, 64, 12, 3, 1, 16, 0), (1, 37, 50, 64, 8, 3, 1, 4, 0), (1, 183, 185, 32, 32, 5, 1, 8, 6),
+    # channel counts that are no multiple of 32 (chunk table), 8 x 8 tiles, up to 16 column tiles
+    (1, 135, 181, 48, 80, 3, 2, 4, 6), (1, 50, 41, 24, 16, 5, 1, 2, 6), (2, 60, 77, 72, 160, 3, 1, 8, 6),
+    (1, 90, 70, 104, 60, 1, 1, 1, 6), (1, 70, 64, 120, 224, 3, 1, 8, 6), (1, 90, 100, 40, 40, 3, 1, 16, 6),
+    (3, 290, 310, 16, 28, 3, 1, 8, 6), (1, 140, 170, 48, 132, 3, 1, 8, 6),
+    (1, 64, 75, 136, 40, 3, 1, 8, 6), (1, 70, 66, 144, 60, 5, 2, 8, 6), (1, 60, 51, 248, 20, 3, 1, 4, 6),
+    (1, 190, 185, 96, 96, 3, 1, 8, 6),
     (1, 281, 290, 32, 48, 3, 2, 4, 6), (9, 160, 240, 32, 40, 3, 1, 8, 0), (5, 250, 243, 32, 100, 1, 1, 16, 0),
 ]
 
@@ -59,6 +65,30 @@ def test_tile_kernel(case, caller):
         z = layer._z.cpu().numpy()
         y = layer.activation().view(torch.int16).cpu().numpy().view(np.uint16).reshape(z.shape)
         assert np.array_equal(y, O.f32_to_bf16_rne(np.maximum(z, 0.0).astype(np.float32))), (case, t)
+    layer.close()
+
+
+@pytest.mark.parametrize("ci", [24, 64])
+def test_tile_kernel_keeps_infinities(ci):
+    """One infinite input value reaches exactly the sites whose support holds it, as an infinity: what the product
+    reads past K is a zero, not a neighbour's value times a zero weight."""
+    rng = np.random.Generator(np.random.PCG64(9))
+    wt = (rng.integers(1, 4, (32, ci, 3, 3)) * rng.choice([-1, 1], (32, ci, 3, 3))).astype(np.float32)
+    n, h, w = (1, 40, 40) if ci == 24 else (1, 185, 184)
+    layer, orc = _layer_pair(wt, n=n, h=h, w=w, dtype="bf16", eps=0.0, block=8, keep_stats=False)
+    assert layer.fused_variant == 6
+    x = rng.integers(0, 4, (n, h, w, ci)).astype(np.float32)
+    for t in range(2):
+        if t == 1:
+            x = x.copy()
+            x[0, 17, 21, ci - 1] = np.inf
+        xs = syn.to_storage(x, "bf16")
+        layer.step(to_device(xs, "bf16"))
+        ref = orc.step(xs)["z"]
+        z = layer._z.cpu().numpy()
+        assert np.array_equal(np.isnan(z), np.isnan(ref)) and np.array_equal(np.isinf(z), np.isinf(ref))
+        ok = ~np.isnan(ref)
+        assert np.array_equal(z[ok].astype(np.float64), ref[ok])
     layer.close()
 
 
