@@ -189,6 +189,22 @@ struct HaloParams {
 bool tile_shape(HaloParams& hp, int ntiles_n, int ksteps, int c, int learned, int lds_limit);
 int tile_occupancy(const HaloParams& hp, int ntiles_n, int ksteps);
 
+// One-launch tile kernel of fp32 layers (sc_tile_f32.hip).
+struct TileF32Params {
+  const void* wpack;   // its own weight layout (launch_pack_tile_f32), groups * ntiles_n KiB
+  int hh, hw;          // halo of an 8 x 8-site tile
+  int cpad, pstride;   // channels padded to 16; LDS bytes per halo pixel
+  int groups;          // 16-channel groups over all taps
+  int lg_group;        // log2 of the lanes that hold a pixel's chunks
+  int ns, shares;      // 16-column tiles per workgroup; workgroups per tile
+  int deal;            // 1: tiles dealt to the XCDs one by one, 0: in contiguous ranges
+};
+bool tile_f32_shape(TileF32Params& t, int c, int k, int stride, int ntn, long tiles, int num_cu, long lds_limit);
+int tile_f32_occupancy(const TileF32Params& t);  // as tile_occupancy
+hipError_t launch_tile_f32(const GateParams& g, const ConvParams& c, const TileF32Params& t, hipStream_t st);
+hipError_t launch_pack_tile_f32(const void* w, void* out, int c_out, int c_in, int k, const TileF32Params& t, int ntn,
+                                hipStream_t st);
+
 // Fused single-pass step for dense bf16 layers (see sc_fused.hip). `g` carries
 // the gate geometry of the fused tiling (ts, tiles, staging rows).
 struct FusedParams {

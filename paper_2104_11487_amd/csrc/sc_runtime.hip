@@ -59,7 +59,8 @@ struct Geometry {
   bool tile;            // one-launch tile kernel: reference frames and translated steps
   bool tile_plain;      // ... and plain steps
   sc::HaloParams tp;
-  int t_tiles_y, t_tiles_x;
+  sc::TileF32Params tf;  // fp32 layers (tp unused): their tile kernel
+  int t_tiles_y, t_tiles_x, t_copy_in_halo;
   bool fused;           // single-pass kernel instead of gate + compaction + conv
   int f_ts, f_tiles_y, f_tiles_x, f_grid, f_copy_in_halo;
   int f_nsplit;         // workgroups per tile of the register-operand kernel (output channels split)
@@ -70,7 +71,7 @@ struct Geometry {
   int f_pstage, f_off_part;
   int vec;              // gate load width (elements)
   size_t elem;
-  size_t off_wpack, off_slot0, off_slot1, off_z, off_y, off_bmask, off_tflag, off_list, off_ctr,
+  size_t off_wpack, off_wtile, off_slot0, off_slot1, off_z, off_y, off_bmask, off_tflag, off_list, off_ctr,
       off_stat, off_smask, off_phi, off_r32, off_rb, off_prev, off_z2, off_wlist, off_wctr,
       off_ftiles, total;
   int learned;          // learned gate: its kernel size (the layer's k), else 0
@@ -354,9 +355,9 @@ int derive(const skipconv_desc* d, Geometry* g, char* err) {
       if (!sc::tile_shape(H, G.ntn, G.ksteps, d->c_in, G.learned, (int)limit)) continue;
       G.t_tiles_y = (G.h_out + H.rows - 1) / H.rows;
       G.t_tiles_x = (G.w_out + H.side - 1) / H.side;
-      G.tile = halo_covers_owned(d->h, G.h_out, H.rows, G.t_tiles_y, s, pad, k) &&
-               halo_covers_owned(d->w, G.w_out, H.side, G.t_tiles_x, s, pad, k);
-      if (!G.tile) break;
+      G.t_copy_in_halo = halo_covers_owned(d->h, G.h_out, H.rows, G.t_tiles_y, s, pad, k) &&
+                         halo_covers_owned(d->w, G.w_out, H.side, G.t_tiles_x, s, pad, k);
+      G.tile = true;
     }
     // plain steps: few tiles per CU, where two kernels are mostly latency, and
     // blocks smaller than 8, whose other convolution gathers site by site.
@@ -367,6 +368,22 @@ int derive(const skipconv_desc* d, Geometry* g, char* err) {
     // channel counts whose other convolution gathers site by site.
     G.tile_plain = G.tile && (G.learned || mixed || (d->c_in <= 64 && (G.ntn == 2 || G.ntn == 4) &&
                                             (tiles16 <= 2 * kCuGuess || b < 8)));
+  }
+
+  // fp32 layers of 24 to 128 channels: 8 x 8-site tiles, norm gates
+  if (!depthwise && d->dtype == SKIPCONV_F32 && d->c_out % 4 == 0 && (b & (b - 1)) == 0 && b <= 8 && !G.learned &&
+      !(d->flags & (SKIPCONV_FLAG_SPLIT_PIPELINE | SKIPCONV_FLAG_EMIT_RESIDUAL | SKIPCONV_FLAG_LARGE_GATE_TILES)) &&
+      (long)d->h * d->w * d->c_in * 4 < (1L << 31) && (long)G.h_out * G.w_out * d->c_out * 4 < (1L << 31)) {
+    G.t_tiles_y = (G.h_out + 7) / 8;
+    G.t_tiles_x = (G.w_out + 7) / 8;
+    const long tiles = (long)d->n * G.t_tiles_y * G.t_tiles_x;
+    G.tile = sc::tile_f32_shape(G.tf, d->c_in, k, s, G.ntn, tiles, kCuGuess, kFusedLdsLimit);
+    // (per-site gates on larger frames of 128 output channels: a whole tile's
+    // product for a few sites; 256 x 256, 128 -> 128, 7 % of the sites: 75 us
+    // against 64 by the gathering convolution)
+    G.tile_plain = G.tile && !(b < 4 && G.ntn >= 8 && tiles >= 3 * kCuGuess);
+    G.t_copy_in_halo = halo_covers_owned(d->h, G.h_out, 8, G.t_tiles_y, s, pad, k) &&
+                       halo_covers_owned(d->w, G.w_out, 8, G.t_tiles_x, s, pad, k);
   }
 
   // fused single-pass kernel: dense bf16, C_in % 32 == 0, tiles of <= 16 x 16
@@ -538,6 +555,8 @@ int derive(const skipconv_desc* d, Geometry* g, char* err) {
   G.off_wpack = off; off = align_up(off + G.wpack_bytes);
   // the x_{t-1} ping-pong slots (none when the caller retains its frames)
   const size_t slot_bytes = (d->flags & SKIPCONV_FLAG_CALLER_RETAINS) ? 0 : G.x_bytes;
+  G.off_wtile = off;
+  if (G.tile && d->dtype == SKIPCONV_F32) off = align_up(off + (size_t)G.tf.groups * G.ntn * 1024);
   G.off_slot0 = off; off = align_up(off + slot_bytes);
   G.off_slot1 = off; off = align_up(off + slot_bytes);
   G.off_z = off; off = align_up(off + G.z_bytes);
@@ -900,12 +919,18 @@ void end_list(skipconv_layer* h) {
   h->wslot ^= 1;
 }
 
-// A plain or translated step as one launch of the tile kernel.
+// A plain or (bf16) translated step as one launch of the tile kernel.
 hipError_t launch_tile(skipconv_layer* h, sc::GateParams gp, const sc::ConvParams& cp, hipStream_t st) {
   gp.tiles_y = h->g.t_tiles_y;
   gp.tiles_x = h->g.t_tiles_x;
+  gp.copy_in_halo = h->g.t_copy_in_halo;
   h->list_valid = false;
   h->work_kind = 3;
+  if (h->d.dtype == SKIPCONV_F32) {
+    sc::TileF32Params tf = h->g.tf;
+    tf.wpack = h->ws + h->g.off_wtile;
+    return sc::launch_tile_f32(gp, cp, tf, st);
+  }
   return sc::launch_tile(gp, cp, h->g.tp, st);
 }
 
@@ -1059,7 +1084,9 @@ int skipconv_create(const skipconv_desc* d, const void* weights, void* workspace
   // 17.0 -> 14.2 us); before that they win (64 -> 64, 160 x 160: 12.8 against
   // 13.4 us, 128 x 96: 7.0 against 12 us; 1 x 1 128 -> 64, 136 x 136: 10.6
   // against 12.8 us).
-  if (h->g.tile && sc::tile_occupancy(h->g.tp, h->g.ntn, h->g.ksteps) < 1) h->g.tile = h->g.tile_plain = false;
+  if (h->g.tile && (d->dtype == SKIPCONV_F32 ? sc::tile_f32_occupancy(h->g.tf)
+                                             : sc::tile_occupancy(h->g.tp, h->g.ntn, h->g.ksteps)) < 1)
+    h->g.tile = h->g.tile_plain = false;
   if (h->g.fused) {
     const long wgs = (long)h->g.f_grid * h->g.f_nsplit;
     if (h->g.tile && h->g.f_mw == 1 && wgs > (d->c_in <= 64 && (h->g.ksteps <= 9 || h->g.ntn >= 8) ? 1 : 2) * (long)h->num_cu) {
@@ -1101,6 +1128,8 @@ int skipconv_create(const skipconv_desc* d, const void* weights, void* workspace
       e = sc::launch_pack_mfma(weights, h->wpack(), d->dtype, d->c_out, d->c_in, d->kernel,
                                g.ksteps, g.ntn, st);
   }
+  if (e == hipSuccess && h->g.tile && d->dtype == SKIPCONV_F32)
+    e = sc::launch_pack_tile_f32(weights, h->ws + g.off_wtile, d->c_out, d->c_in, d->kernel, g.tf, g.ntn, st);
   if (e == hipSuccess && g.fused)
     e = sc::launch_fused_tiles(reinterpret_cast<uint32_t*>(h->ws + g.off_ftiles), g.f_grid, g.f_tiles_y,
                                g.f_tiles_x, st);
@@ -1233,7 +1262,7 @@ int skipconv_step_translated(skipconv_t h, const void* x_t, int32_t dy, int32_t 
   // block-halo convolution reads z_{t-1} from the old slot at the shifted site
   // and moves the state of the blocks that are off itself.
   const float* z_old = h->z();
-  const bool tile = g.tile && !g.learned;
+  const bool tile = g.tile && !g.learned && d.dtype == SKIPCONV_BF16;
   const bool zshift = tile || (g.halo && !g.depthwise);
   hipError_t e = hipSuccess;
   if (!zshift)
@@ -1338,6 +1367,19 @@ int skipconv_step_chained(skipconv_t h, skipconv_t up, void* stream, const float
     gp.up_block = up->d.block;
     gp.up_hb = up->g.hb;
     gp.up_wb = up->g.wb;
+  }
+  if (g.tile_plain) {  // the kernel of the layer's plain steps, on the residual
+    gp.rin = 1;
+    sc::ConvParams cp = conv_geometry(d, g, false);
+    cp.wpack = h->wpack();
+    cp.z = h->z();
+    cp.y = h->y();
+    const hipError_t e = launch_tile(h, gp, cp, st);
+    if (e != hipSuccess) return hip_fail(h, e, "chained tile launch");
+    h->ref_pending = false;
+    ++h->frames;
+    if (z_t) *z_t = h->z();
+    return SKIPCONV_OK;
   }
   StepList sl{};
   hipError_t e = begin_list(h, gp, st, &sl);

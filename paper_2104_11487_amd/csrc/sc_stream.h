@@ -102,12 +102,38 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t frame_rsrc(const void* base, u
 }
 constexpr uint32_t kOutOfRange = 0x80000000u;  // byte offset past every frame resource
 
+// Copy the pixels [y0, y1) x [x0, x1) of one image from `src` to `dst` (frame
+// resources; px16 16-byte words a pixel, w pixels a row), by `threads` threads
+// of a workgroup: the owned pixels of a tile whose halo does not hold them all
+// (strides larger than the kernel).
+template <typename R>
+__device__ __forceinline__ void copy_pixels(R src, R dst, int y0, int y1, int x0, int x1, int w, int px16, int threads) {
+  const int per_row = max(x1 - x0, 0) * px16, total = max(y1 - y0, 0) * per_row;
+  for (int i = threadIdx.x; i < total; i += threads) {
+    const int yy = i / per_row, e = i - yy * per_row;
+    const uint32_t off = (uint32_t)(((y0 + yy) * w + x0) * px16 + e) * 16u;
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_amdgcn_raw_buffer_load_b128(src, off, 0, 0), dst, off, 0, 2);
+  }
+}
+
 // Workgroup b runs tile remap(b): XCD b % 8 (workgroups go to the XCDs
 // round-robin) receives a contiguous range of tiles, so neighbouring tiles
 // share their halo rows through one L2.
 __device__ __forceinline__ int xcd_tile(int b, int g) {
   const int per = g >> 3, rem = g & 7, x = b & 7;
   return x * per + min(x, rem) + (b >> 3);
+}
+
+// Workgroup b runs tile xcd_deal(b): runs of G tiles are dealt to the XCDs in
+// turn. Neighbours within a run share an L2, and a cluster of active tiles (a
+// moving object) is spread over every XCD, where a contiguous range would leave
+// its products to one XCD's CUs.
+template <int G>
+__device__ __forceinline__ int xcd_deal(int b, int g) {
+  const int full = g / (8 * G) * (8 * G);
+  if (b >= full) return b;
+  const int i = b >> 3;
+  return (i / G * 8 + (b & 7)) * G + i % G;
 }
 
 }  // namespace sc

@@ -8,7 +8,8 @@ torch = pytest.importorskip("torch")
 
 from oracle import skipconv_oracle as O  # noqa: E402
 from paper_2104_11487_amd import synthetic as syn  # noqa: E402
-from parity_util import compare_frame, eps_for_density, say, to_device  # noqa: E402
+from paper_2104_11487_amd import skipconv as S  # noqa: E402
+from parity_util import compare_frame, eps_for_density, say, to_device, weight_storage  # noqa: E402
 from test_gpu_parity import _layer_pair, oracle_stats  # noqa: E402
 
 pytestmark = pytest.mark.gpu
@@ -26,7 +27,7 @@ CASES = [
     (1, 90, 70, 104, 60, 1, 1, 1, 6), (1, 70, 64, 120, 224, 3, 1, 8, 6), (1, 90, 100, 40, 40, 3, 1, 16, 6),
     (3, 290, 310, 16, 28, 3, 1, 8, 6), (1, 140, 170, 48, 132, 3, 1, 8, 6),
     (1, 64, 75, 136, 40, 3, 1, 8, 6), (1, 70, 66, 144, 60, 5, 2, 8, 6), (1, 60, 51, 248, 20, 3, 1, 4, 6),
-    (1, 190, 185, 96, 96, 3, 1, 8, 6),
+    (1, 190, 185, 96, 96, 3, 1, 8, 6), (1, 75, 90, 48, 32, 1, 2, 4, 6), (3, 290, 350, 32, 64, 1, 2, 8, 6),
     (1, 281, 290, 32, 48, 3, 2, 4, 6), (9, 160, 240, 32, 40, 3, 1, 8, 0), (5, 250, 243, 32, 100, 1, 1, 16, 0),
 ]
 
@@ -108,6 +109,38 @@ def test_tile_kernel_integer_frames_are_the_dense_convolution():
     layer.close()
 
 
+# fp32 layers: 24 to 128 channels, padded channels (24, 40), 1 to 8 workgroups per tile and 1 to 4 column tiles
+# each, stride 2, partial output columns, every block size: (n, h, w, c_in, c_out, k, stride, block)
+F32 = [(1, 41, 52, 64, 64, 3, 1, 8), (1, 50, 43, 24, 48, 3, 1, 1), (2, 37, 60, 40, 20, 3, 2, 4), (1, 30, 29, 128, 128, 3, 1, 8),
+       (2, 170, 165, 32, 64, 1, 1, 2), (1, 21, 33, 48, 12, 5, 1, 4), (2, 130, 140, 32, 128, 1, 1, 8), (1, 60, 50, 64, 24, 1, 2, 8),
+       (1, 25, 30, 56, 100, 5, 2, 1)]
+
+
+@pytest.mark.parametrize("case", F32, ids=["x".join(map(str, c)) for c in F32])
+def test_tile_kernel_f32(case):
+    n, h, w, ci, co, k, s, b = case
+    rng = np.random.Generator(np.random.PCG64(90 + ci + co + k + b))
+    frames = list(syn.RectVideo(h, w, ci, 5, seed=91 + ci + b, batch=n, n_rect=3, side_lo=5, side_hi=14))
+    wt = rng.normal(0, 0.15, (co, ci, k, k)).astype(np.float32)
+    pad = (k - 1) // 2
+    ho, wo = O.out_size(h, k, s, pad), O.out_size(w, k, s, pad)
+    eps = eps_for_density(oracle_stats(frames[:2], wt.shape, dtype="f32", stride=s), b, ho, wo, 0.3)
+    layer, orc = _layer_pair(wt, n=n, h=h, w=w, dtype="f32", eps=eps, block=b, stride=s, act_out="relu", translate=True)
+    assert layer.fused_variant == 6, (case, layer.fused_variant)
+    for t, f in enumerate(frames):
+        if t == 4:
+            layer.reset()
+            orc.reset()
+        d = (s, 0) if t == 2 else (0, 0)  # a translated step between plain ones
+        layer.step_translated(to_device(f, "f32"), *d)
+        ref = orc.step(f, shift=d)
+        say(f"[tile f32 {case}] frame {t}")
+        compare_frame(layer, ref, "f32", t=t, tag=f"tile f32 {case}", keep_stats=True)
+        z = layer._z.cpu().numpy()
+        assert np.array_equal(layer.activation().cpu().numpy().reshape(z.shape), np.maximum(z, np.float32(0))), (case, t)
+    layer.close()
+
+
 # learned gate (Eq. 8) in the tile kernel: every column build, both tile
 # heights, 3 x 3 and 1 x 1 (taps shared by one, two or four thread groups)
 LEARNED = [(1, 181, 187, 64, 64, 3, 8), (1, 150, 141, 32, 20, 3, 1), (3, 170, 171, 64, 64, 3, 16), (1, 41, 70, 64, 12, 3, 16),
@@ -138,3 +171,36 @@ def test_tile_kernel_learned_gate(case, stats):
         compare_frame(layer, ref, "bf16", t=t, tag=f"tile learned {case}", keep_stats=stats)
         assert t == 0 or t == 3 or 0 < ref["count"] < ref["block_mask"].size, "the gate decides nothing"
     layer.close()
+
+
+# (n, h, w, c_in, c_out, k, block, dtype, learned)
+CHAIN = [(1, 181, 187, 64, 64, 3, 8, "bf16", False), (3, 170, 171, 64, 32, 3, 16, "bf16", False), (1, 60, 75, 48, 80, 3, 4, "bf16", False),
+         (1, 60, 51, 136, 20, 1, 2, "bf16", False), (1, 181, 187, 64, 64, 3, 8, "bf16", True), (1, 190, 181, 32, 32, 1, 4, "bf16", True),
+         (1, 40, 52, 64, 64, 3, 8, "f32", False), (1, 30, 41, 40, 128, 3, 1, "f32", False)]
+
+
+@pytest.mark.parametrize("case", CHAIN, ids=["x".join(map(str, c)) for c in CHAIN])
+def test_chained_step_is_the_plain_step_bit_for_bit(case):
+    n, h, w, ci, co, k, b, dtype, learned = case
+    rng = np.random.Generator(np.random.PCG64(11 + ci + co + k + b))
+    vid = list(syn.RectVideo(h, w, 8, 4, seed=12 + b, batch=n, n_rect=2, side_lo=5, side_hi=20, noise_std=0.0))
+    w0 = to_device(weight_storage(rng.normal(0, 0.3, (ci, 8, 1, 1)).astype(np.float32), dtype), dtype)
+    w1 = to_device(weight_storage(rng.normal(0, 0.1, (co, ci, k, k)).astype(np.float32), dtype), dtype)
+    up = S.SkipConv(w0, n=n, h=h, w=w, eps=0.0, block=b, act_out="relu", emit_residual=True)
+    kw = dict(n=n, h=h, w=w, eps=0.2, block=b, act_out="identity", keep_stats=True, gate="learned" if learned else "input")
+    one, two = S.SkipConv(w1, **kw), S.SkipConv(w1, **kw)
+    assert one.fused_variant == 6
+    for layer in (one, two):
+        if learned:
+            layer.set_gate_weights(torch.from_numpy(np.random.Generator(np.random.PCG64(3)).normal(
+                0, 0.1, (ci, k, k)).astype(np.float32)).cuda(), -0.05)
+    for t, f in enumerate(vid):
+        up.step(to_device(syn.to_storage(f, dtype), dtype))
+        za = one.step_chained(up)
+        zb = two.step(up.activation().clone())
+        torch.cuda.synchronize()
+        assert torch.equal(za, zb), (case, t)
+        assert np.array_equal(one.block_mask(), two.block_mask()) and torch.equal(one.activation(), two.activation())
+        assert np.array_equal(one.stat().view(np.uint32), two.stat().view(np.uint32))
+    for layer in (up, one, two):
+        layer.close()
