@@ -366,8 +366,13 @@ int derive(const skipconv_desc* d, Geometry* g, char* err) {
     // 128 channels on either side 2 x 256 x 256 33.5 / 30.6 and 55 / 46.
     // The learned gate is VALU work, so its tiles gain at every size, and so do
     // channel counts whose other convolution gathers site by site.
+    // 128 input channels with blocks smaller than 8 gain with every output width
+    // (300 x 300, 128 -> 32 / 128: 42.0 -> 24.6, 47.3 -> 31.1 us; 2 x 500 x 500
+    // 128 -> 128, 5 % covered: 125.5 -> 122.6), fewer only up to 64 outputs (1 x 1
+    // 64 -> 128, 300 x 500: 21.8 against 24.3 us by the gathering convolution).
     G.tile_plain = G.tile && (G.learned || mixed || (d->c_in <= 64 && (G.ntn == 2 || G.ntn == 4) &&
-                                            (tiles16 <= 2 * kCuGuess || b < 8)));
+                                                     (tiles16 <= 2 * kCuGuess || b < 8)) ||
+                              (b < 8 && d->c_in == 128 && G.ntn >= 2));
   }
 
   // fp32 layers of 24 to 128 channels: 8 x 8-site tiles, norm gates
