@@ -367,12 +367,14 @@ int derive(const skipconv_desc* d, Geometry* g, char* err) {
     // The learned gate is VALU work, so its tiles gain at every size, and so do
     // channel counts whose other convolution gathers site by site.
     // 128 input channels with blocks smaller than 8 gain with every output width
-    // (300 x 300, 128 -> 32 / 128: 42.0 -> 24.6, 47.3 -> 31.1 us; 2 x 500 x 500
+    // from a workgroup per CU on (128 -> 128, 192 x 192: 24.9 -> 21.3 us; 152 x 152:
+    // 19.5 against 20.6 us;
+    // 300 x 300, 128 -> 32 / 128: 42.0 -> 24.6, 47.3 -> 31.1 us; 2 x 500 x 500
     // 128 -> 128, 5 % covered: 125.5 -> 122.6), fewer only up to 64 outputs (1 x 1
     // 64 -> 128, 300 x 500: 21.8 against 24.3 us by the gathering convolution).
     G.tile_plain = G.tile && (G.learned || mixed || (d->c_in <= 64 && (G.ntn == 2 || G.ntn == 4) &&
                                                      (tiles16 <= 2 * kCuGuess || b < 8)) ||
-                              (b < 8 && d->c_in == 128 && G.ntn >= 2));
+                              (b < 8 && d->c_in == 128 && G.ntn >= 2 && 2 * tiles16 > kCuGuess));
   }
 
   // fp32 layers of 24 to 128 channels: 8 x 8-site tiles, norm gates
@@ -1085,16 +1087,24 @@ int skipconv_create(const skipconv_desc* d, const void* weights, void* workspace
   // The one-launch tile kernel takes over from the 8 x 8-tile kernels once
   // their workgroups come in more than two rounds (64 -> 64, one 180 x 180
   // frame: 17.2 -> 15.4 us; 256 x 256: 23.7 -> 17.7 us), or more than one where
-  // K is short or the output wide (160 x 160: 32 -> 32 9.4 -> 7.8 us, 64 -> 128
-  // 17.0 -> 14.2 us); before that they win (64 -> 64, 160 x 160: 12.8 against
-  // 13.4 us, 128 x 96: 7.0 against 12 us; 1 x 1 128 -> 64, 136 x 136: 10.6
-  // against 12.8 us).
+  // the output is wide (160 x 160, 64 -> 128: 17.0 -> 14.2 us) or, at stride 1,
+  // the product is short (32 -> 32 9.4 -> 7.8 us; 1 x 1 64 -> 32 9.0 -> 7.7 us);
+  // before that they win (64 -> 64, 160 x 160: 12.8 against 13.4 us, 128 x 96:
+  // 7.0 against 12 us; 32 -> 64 8.4 against 9.2 us; 32 -> 32 at stride 2, 19 x 19
+  // tiles, 10.8 against 14.5 us). Layers with much staging for little product
+  // keep the 8 x 8 tiles to three rounds (24 x 24 / 28 x 28 tiles: 32 -> 32 at
+  // stride 2 14.9 against 16.2 / 18.9 against 16.7 us, 128 -> 32 18.9 against 20.5 /
+  // 24.2 against 22.1 us), 128 -> 64 to the end (1 x 1, 31 x 31: 16.6 against 17.0).
   if (h->g.tile && (d->dtype == SKIPCONV_F32 ? sc::tile_f32_occupancy(h->g.tf)
                                              : sc::tile_occupancy(h->g.tp, h->g.ntn, h->g.ksteps)) < 1)
     h->g.tile = h->g.tile_plain = false;
   if (h->g.fused) {
     const long wgs = (long)h->g.f_grid * h->g.f_nsplit;
-    if (h->g.tile && h->g.f_mw == 1 && wgs > (d->c_in <= 64 && (h->g.ksteps <= 9 || h->g.ntn >= 8) ? 1 : 2) * (long)h->num_cu) {
+    const bool early = d->c_in <= 64 && (h->g.ntn >= 8 || (d->stride == 1 && h->g.ksteps <= 9 &&
+                                                           (h->g.ntn == 2 || d->kernel == 1)));
+    const bool late = (d->c_in == 128 && h->g.ntn == 2) || (d->c_in < 64 && d->stride > 1 && d->kernel > 1);
+    const int rounds = early ? 1 : (d->c_in == 128 && h->g.ntn == 4) ? 4 : late ? 3 : 2;
+    if (h->g.tile && h->g.f_mw == 1 && wgs > rounds * (long)h->num_cu) {
       h->g.fused = false;
       h->g.tile_plain = true;
     } else {
