@@ -297,6 +297,8 @@ tile_kernel(GateParams g, ConvParams c, HaloParams hp) {
       }
       lds_barrier();  // the next chunks overwrite the buffer
     }
+    // without a score no barrier has passed since the block flags were cleared
+    if (kSplit == 1 && !score) lds_barrier();
     // the owned pixels' state copy, past the loads that the scores waited for
     each([&](int u, int q, bool valid) {
       const int hy = qdiv(q, inv_hw), hx = q - hy * hw;

@@ -144,14 +144,15 @@ def test_tile_kernel_f32(case):
 # learned gate (Eq. 8) in the tile kernel: every column build, both tile
 # heights, 3 x 3 and 1 x 1 (taps shared by one, two or four thread groups)
 LEARNED = [(1, 181, 187, 64, 64, 3, 8), (1, 150, 141, 32, 20, 3, 1), (3, 170, 171, 64, 64, 3, 16), (1, 41, 70, 64, 12, 3, 16),
-           (1, 37, 50, 32, 8, 3, 4), (1, 190, 180, 64, 128, 1, 4), (2, 150, 170, 64, 100, 3, 2), (1, 190, 181, 32, 32, 1, 8)]
+           (1, 37, 50, 32, 8, 3, 4), (1, 190, 180, 64, 128, 1, 4), (2, 150, 170, 64, 100, 3, 2), (1, 190, 181, 32, 32, 1, 8),
+           (9, 128, 128, 32, 12, 3, 2)]  # one thread per site: the clearing of the flags needs a barrier of its own
 
 
 @pytest.mark.parametrize("stats", [True, False], ids=["stats", "nostats"])
 @pytest.mark.parametrize("case", LEARNED, ids=["x".join(map(str, c)) for c in LEARNED])
 def test_tile_kernel_learned_gate(case, stats):
     n, h, w, ci, co, k, b = case
-    if not stats and n * h * w > 10000:
+    if not stats and n * h * w > 10000 and n < 9:
         pytest.skip("covered on the smaller frames")
     rng = np.random.Generator(np.random.PCG64(70 + ci + co + k + b))
     frames = list(syn.RectVideo(h, w, ci, 4, seed=71 + ci + b, batch=n, n_rect=3, side_lo=9, side_hi=30))
