@@ -16,7 +16,7 @@
 //      rho to LDS, x_t of owned pixels to the spare x_{t-1} slot;
 //   2. support sums, threshold, block flags in LDS and in memory;
 //   3. product of the tile's 16 * WM * WAVES_M sites in one pass (a wave whose
-//      sites are all off skips it), z_{t-1} loaded before it, then the stores.
+//      sites are all off skips it), z_{t-1} added, then the stores.
 //      One pass, because loads issued after a store wait for it: two passes of
 //      128 sites took 3 us more on 2 x 256 x 256 x 64.
 // On a reference frame every block is on and x_{t-1} is not read: the frame
@@ -56,10 +56,13 @@ __device__ __forceinline__ float group_sum_lg(float v, int lg) {
   return group_sum<2>(v);
 }
 
-// OCC: waves per SIMD the register budget aims for. ZI: the accumulators start
-// from z_{t-1}; otherwise it is added after the product (one rounding of the
-// update on the state, as in the kernels this one takes over from).
-template <int WAVES_M, int WAVES_N, int WM, int WN, int KR, int OCC, int KI, bool ZI, bool TRANS, bool CHAIN, int LEARN,
+// OCC: waves per SIMD the register budget aims for. z_{t-1} is added after the
+// product (one rounding of the update on the state: 1.1e-7 from the exact
+// sums at 48 -> 128 channels, 1.3e-7 when the sums start from z_{t-1}). LATE: it
+// is loaded after the product too, where it would not fit the registers beside
+// the sums (2 x 280 x 280, 48 -> 128: 46.5 us, started from z_{t-1} 41.4, by the
+// gathering convolution 79.7; 2 x 256 x 256 x 64 translated 31.1, 31.2 and 66.2).
+template <int WAVES_M, int WAVES_N, int WM, int WN, int KR, int OCC, int KI, bool LATE, bool TRANS, bool CHAIN, int LEARN,
           bool TAB>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) __attribute__((amdgpu_waves_per_eu(OCC)))
 tile_kernel(GateParams g, ConvParams c, HaloParams hp) {
@@ -390,20 +393,22 @@ tile_kernel(GateParams g, ConvParams c, HaloParams hp) {
     if (__ballot(T.live != 0u) == 0ull) return;
     if (exposed) H.start_b(bq);
     typename HC::Acc zo, acc;
-    H.load_z(zo, T, false);
+    if constexpr (!LATE) H.load_z(zo, T, false);
 #pragma unroll
     for (int i = 0; i < WM; ++i)
 #pragma unroll
-      for (int jn = 0; jn < WN; ++jn) acc[i][jn] = ZI ? zo[i][jn] : floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+      for (int jn = 0; jn < WN; ++jn) acc[i][jn] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
     H.product(acc, bq);
-    if constexpr (!ZI) {
-#pragma unroll
-      for (int i = 0; i < WM; ++i)
-#pragma unroll
-        for (int jn = 0; jn < WN; ++jn)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) acc[i][jn][v] = __fadd_rn(zo[i][jn][v], acc[i][jn][v]);
+    if constexpr (LATE) {
+      asm volatile("" ::: "memory");  // not moved up into the product's registers
+      H.load_z(zo, T, false);
     }
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+      for (int jn = 0; jn < WN; ++jn)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[i][jn][v] = __fadd_rn(zo[i][jn][v], acc[i][jn][v]);
     H.store(T, acc);
   };
   product(false);
@@ -458,9 +463,9 @@ tile_kernel(GateParams g, ConvParams c, HaloParams hp) {
 }
 
 // Builds by tile extent (16 x 16, 8 x 16 or 8 x 8 sites) and 16-column output
-// tiles: rows, columns, ntn, WAVES_M, WAVES_N, WM, WN, KR and ZI of plain
-// steps, KR of translated steps (which start the accumulators from z: with z
-// held beside them the 128-register builds spill), OCC, KI.
+// tiles: rows, columns, ntn, WAVES_M, WAVES_N, WM, WN, KR and LATE of plain
+// steps, KR of translated steps (all LATE: with z beside the sums the
+// 128-register builds spill), OCC, KI.
 #define SC_TILE_BUILDS(X)                                                                                 \
   X(16, 16, 1, 4, 1, 4, 1, 4, false, 4, 3, 6) X(16, 16, 2, 4, 2, 4, 1, 4, false, 4, 4, 3)                 \
   X(16, 16, 4, 4, 2, 4, 2, 2, false, 4, 4, 3) X(16, 16, 8, 4, 2, 4, 4, 2, true, 2, 2, 3)                  \
