@@ -29,7 +29,8 @@
 // KR: B register ring (0 picks 8 / 6 / 4 by WN). KU: halo items (two 16-byte
 // loads each) in flight per thread. ADB: A fragment register sets (2: the next
 // step's fragments are read before this step's MFMAs; 1: M-tile by M-tile
-// after them).
+// after them). FL: k-steps of a chain of MFMAs whose sum is then added to the
+// accumulators (0: one chain over K).
 #pragma once
 
 #include "sc_device.h"
@@ -56,10 +57,12 @@ struct HaloTile {
   uint32_t live;  // MASK: bit i: this lane's site of M-tile i is updated
 };
 
-template <int WAVES_M, int WAVES_N, int WM, int WN, int KR, int KU, int ADB, bool TRANS, bool MASK = false, bool TAB = false>
+template <int WAVES_M, int WAVES_N, int WM, int WN, int KR, int KU, int ADB, bool TRANS, bool MASK = false, bool TAB = false,
+          int FL = 0>
 struct HaloConv {
   static constexpr int kThreads = 64 * WAVES_M * WAVES_N;
   static constexpr int kR = KR ? KR : (WN <= 2 ? 8 : (WN == 3 ? 6 : 4));  // even
+  static_assert(FL == 0 || (ADB == 1 && kR % FL == 0), "whole chains in a turn of the ring");
   typedef floatx4 Acc[WM][WN];
 
   const ConvParams& p;
@@ -302,18 +305,40 @@ struct HaloConv {
         for (int jn = 0; jn < WN; ++jn)
           acc[i][jn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[jn], a[i], acc[i][jn], 0, 0, 0);
     };
+    // FL: the sum of a chain of FL k-steps joins acc when the next chain starts
+    // from zero; the k-steps past the last whole turn of the ring lengthen the last one
+    Acc chain;
+    auto join = [&](int i, int jn) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[i][jn][v] = __fadd_rn(acc[i][jn][v], chain[i][jn][v]);
+    };
     // one A register set: the fragment of M-tile i for the next step is read
     // right after the MFMAs of M-tile i of this step have taken it
-    auto mfmas_then_read = [&](bf16x8* a, const bf16x8* bf) {
+    auto mfmas_then_read = [&](bf16x8* a, const bf16x8* bf, bool fresh) {
 #pragma unroll
       for (int i = 0; i < WM; ++i) {
 #pragma unroll
-        for (int jn = 0; jn < WN; ++jn)
-          acc[i][jn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[jn], a[i], acc[i][jn], 0, 0, 0);
+        for (int jn = 0; jn < WN; ++jn) {
+          if constexpr (FL > 0) {
+            if (fresh) {
+              join(i, jn);
+              chain[i][jn] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+            }
+            chain[i][jn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[jn], a[i], chain[i][jn], 0, 0, 0);
+          } else {
+            acc[i][jn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[jn], a[i], acc[i][jn], 0, 0, 0);
+          }
+        }
         a[i] = a_at(i);
       }
       advance();
     };
+    if constexpr (FL > 0) {
+#pragma unroll
+      for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int jn = 0; jn < WN; ++jn) chain[i][jn] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
     read_a(aq[0]);
     int ks = 0;
     for (; ks + kR <= ksteps; ks += kR) {
@@ -326,7 +351,7 @@ struct HaloConv {
           mfmas(aq[r & 1], bq[r]);
           __builtin_amdgcn_sched_barrier(0);
         } else {
-          mfmas_then_read(aq[0], bq[r]);
+          mfmas_then_read(aq[0], bq[r], FL > 0 && r % (FL ? FL : 1) == 0);
         }
       }
     }
@@ -337,9 +362,15 @@ struct HaloConv {
           read_a(aq[(r + 1) & 1]);
           mfmas(aq[r & 1], bq[r]);
         } else {
-          mfmas_then_read(aq[0], bq[r]);
+          mfmas_then_read(aq[0], bq[r], false);
         }
       }
+    if constexpr (FL > 0) {
+#pragma unroll
+      for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int jn = 0; jn < WN; ++jn) join(i, jn);
+    }
   }
 
   // the activation output y_old = dtype(act(z_{t-1})) of the tile's sites in

@@ -178,6 +178,7 @@ struct HaloParams {
   int rows;              // one-launch tile kernel: output rows of a tile
   int lg_group;          // one-launch tile kernel: log2 of the lanes that hold a pixel's chunks
   int tab_off;           // one-launch tile kernel: LDS offset of the chunk table (C_in not 32, 64, 128), else 0
+  int parts;             // one-launch tile kernel: 1: the builds that sum K in short chains (sc_tile_parts.hip)
   int part_off;          // one-launch tile kernel: LDS offset of the chunk sums (> 16 chunks a pixel), else 0
 };
 

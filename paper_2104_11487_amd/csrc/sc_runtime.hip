@@ -336,6 +336,7 @@ int derive(const skipconv_desc* d, Geometry* g, char* err) {
       !(d->flags & (SKIPCONV_FLAG_SPLIT_PIPELINE | SKIPCONV_FLAG_EMIT_RESIDUAL | SKIPCONV_FLAG_LARGE_GATE_TILES)) &&
       (long)d->h * d->w * d->c_in * 4 < (1L << 31) && (long)G.h_out * G.w_out * d->c_out * 4 < (1L << 31)) {
     sc::HaloParams& H = G.tp;
+    H.parts = 0;
     // 16 rows read 1.27 x the tile's pixels (8 rows: 1.41 x) but give half the
     // workgroups: 8 rows while 16 x 16 tiles would be fewer than two per CU
     // (one 256 x 256 x 64 frame, translated: 20.3 against 22.6 us; four
@@ -1085,31 +1086,37 @@ int skipconv_create(const skipconv_desc* d, const void* weights, void* workspace
     if (d->c_in > 64 || d->c_out > 64 || h->g.f_grid > cap) h->g.fused = false;
   }
   // The one-launch tile kernel takes over from the 8 x 8-tile kernels once
-  // their workgroups come in more than two rounds (64 -> 64, one 180 x 180
-  // frame: 17.2 -> 15.4 us; 256 x 256: 23.7 -> 17.7 us), or more than one where
-  // the output is wide (160 x 160, 64 -> 128: 17.0 -> 14.2 us) or, at stride 1,
-  // the product is short (32 -> 32 9.4 -> 7.8 us; 1 x 1 64 -> 32 9.0 -> 7.7 us);
+  // their workgroups come in more than two rounds (64 -> 64, one 200 x 200
+  // frame: 17.6 -> 16.3 us; 256 x 256: 23.2 -> 17.4 us), or more than one where
+  // the output is wide (138 x 130, 64 -> 96: 15.4 -> 13.2 us) or, at stride 1,
+  // the product is short (160 x 160, 32 -> 32 9.0 -> 7.5 us; 1 x 1 64 -> 32 9.0 -> 7.7 us);
   // before that they win (64 -> 64, 160 x 160: 12.8 against 13.4 us, 128 x 96:
   // 7.0 against 12 us; 32 -> 64 8.4 against 9.2 us; 32 -> 32 at stride 2, 19 x 19
   // tiles, 10.8 against 14.5 us). Layers with much staging for little product
   // keep the 8 x 8 tiles to three rounds (24 x 24 / 28 x 28 tiles: 32 -> 32 at
-  // stride 2 14.9 against 16.2 / 18.9 against 16.7 us, 128 -> 32 18.9 against 20.5 /
-  // 24.2 against 22.1 us), 128 -> 64 to the end (1 x 1, 31 x 31: 16.6 against 17.0).
-  if (h->g.tile && (d->dtype == SKIPCONV_F32 ? sc::tile_f32_occupancy(h->g.tf)
-                                             : sc::tile_occupancy(h->g.tp, h->g.ntn, h->g.ksteps)) < 1)
-    h->g.tile = h->g.tile_plain = false;
-  if (h->g.fused) {
+  // stride 2 14.9 against 16.2 / 18.9 against 16.7 us), 128 -> 32 and 128 -> 64 to
+  // the end (1 x 1 128 -> 64, 31 x 31: 16.6 against 17.0; 128 -> 32, 28 x 28 tiles,
+  // 24.2 against 22.1 us, where one chain over K = 1152 more than doubled the
+  // distance from the exact sums).
+  bool takes_over = false;
+  if (h->g.tile && h->g.fused && h->g.f_mw == 1) {
     const long wgs = (long)h->g.f_grid * h->g.f_nsplit;
     const bool early = d->c_in <= 64 && (h->g.ntn >= 8 || (d->stride == 1 && h->g.ksteps <= 9 &&
                                                            (h->g.ntn == 2 || d->kernel == 1)));
-    const bool late = (d->c_in == 128 && h->g.ntn == 2) || (d->c_in < 64 && d->stride > 1 && d->kernel > 1);
-    const int rounds = early ? 1 : (d->c_in == 128 && h->g.ntn == 4) ? 4 : late ? 3 : 2;
-    if (h->g.tile && h->g.f_mw == 1 && wgs > rounds * (long)h->num_cu) {
-      h->g.fused = false;
-      h->g.tile_plain = true;
-    } else {
-      h->g.tile = h->g.tile_plain = false;
-    }
+    const bool late = d->c_in < 64 && d->stride > 1 && d->kernel > 1;
+    const int rounds = early ? 1 : (d->c_in == 128 && h->g.ntn <= 4) ? 4 : late ? 3 : 2;
+    // the register-operand kernel gives way only to builds as exact as itself
+    takes_over = wgs > rounds * (long)h->num_cu && (!h->g.f_rb || h->g.tp.rows == 8);
+    h->g.tp.parts = takes_over && h->g.f_rb;
+  }
+  if (h->g.tile && (d->dtype == SKIPCONV_F32 ? sc::tile_f32_occupancy(h->g.tf)
+                                             : sc::tile_occupancy(h->g.tp, h->g.ntn, h->g.ksteps)) < 1)
+    h->g.tile = h->g.tile_plain = takes_over = false;
+  if (takes_over) {
+    h->g.fused = false;
+    h->g.tile_plain = true;
+  } else if (h->g.fused) {
+    h->g.tile = h->g.tile_plain = false;
   }
   h->conv_occ = conv_setup(h->g, d, h->device);
   if (workspace) {

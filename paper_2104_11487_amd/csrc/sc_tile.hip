@@ -6,9 +6,6 @@ namespace sc {
 
 namespace {
 
-// learned gate: halo chunks per thread, all in registers: (rows + 2) x 18
-// pixels of up to 64 channels
-constexpr int kLearnItems(int rows, int waves) { return ((rows + 2) * 18 * 8 + waves * 64 - 1) / (waves * 64); }
 const TileBuild kTileBuilds[] = {
 #define SC_X(rows, cols, ntn, a, b, wm, wn, kr, zi, krt, occ, ki)                                 \
   {rows, cols, ntn, 64 * a * b, tile_kernel<a, b, wm, wn, kr, occ, ki, zi, false, false, 0, false>, \
@@ -24,7 +21,7 @@ const TileBuild kTileBuilds[] = {
 
 const TileBuild* tile_build(const HaloParams& hp, int ntn) {
   int count = (int)(sizeof(kTileBuilds) / sizeof(kTileBuilds[0]));
-  const TileBuild* b = hp.tab_off ? tile_tab_builds(&count) : kTileBuilds;
+  const TileBuild* b = hp.tab_off ? tile_tab_builds(&count) : hp.parts ? tile_parts_builds(&count) : kTileBuilds;
   for (; count > 0; --count, ++b)
     if (b->rows == hp.rows && b->cols == hp.side && b->ntn == ntn) return b;
   return nullptr;

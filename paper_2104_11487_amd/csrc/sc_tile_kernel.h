@@ -29,7 +29,8 @@
 // Chained steps (CHAIN): the input is the upstream layer's fp32 residual; the
 // same arithmetic from there on, so z is that of a plain step bit for bit.
 //
-// The kernel is instantiated in sc_tile.hip (32, 64 or 128 input channels) and
+// The kernel is instantiated in sc_tile.hip (32, 64 or 128 input channels),
+// sc_tile_parts.hip (those whose K is summed in short chains: FL) and
 // sc_tile_tab.hip (other multiples of 8).
 #pragma once
 
@@ -63,12 +64,12 @@ __device__ __forceinline__ float group_sum_lg(float v, int lg) {
 // the sums (2 x 280 x 280, 48 -> 128: 46.5 us, started from z_{t-1} 41.4, by the
 // gathering convolution 79.7; 2 x 256 x 256 x 64 translated 31.1, 31.2 and 66.2).
 template <int WAVES_M, int WAVES_N, int WM, int WN, int KR, int OCC, int KI, bool LATE, bool TRANS, bool CHAIN, int LEARN,
-          bool TAB>
+          bool TAB, int FL = 0>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) __attribute__((amdgpu_waves_per_eu(OCC)))
 tile_kernel(GateParams g, ConvParams c, HaloParams hp) {
   constexpr int kTileThreads = 64 * WAVES_M * WAVES_N;
   static_assert(!TRANS || (!LEARN && !CHAIN), "learned and chained translated steps take the split pipeline");
-  typedef HaloConv<WAVES_M, WAVES_N, WM, WN, KR, 1, 1, TRANS, true, TAB> HC;
+  typedef HaloConv<WAVES_M, WAVES_N, WM, WN, KR, 1, 1, TRANS, true, TAB, FL> HC;
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   __shared__ uint32_t blk_flag[kMaxTileBlocks];
   float* a_halo = reinterpret_cast<float*>(lds + hp.lds_bytes);
@@ -472,6 +473,10 @@ tile_kernel(GateParams g, ConvParams c, HaloParams hp) {
   X(8, 16, 1, 4, 1, 2, 1, 4, false, 4, 4, 4) X(8, 16, 2, 4, 1, 2, 2, 4, false, 4, 4, 4)                   \
   X(8, 16, 4, 2, 2, 4, 2, 2, false, 4, 4, 3) X(8, 16, 8, 2, 4, 4, 2, 2, false, 4, 4, 3)
 
+// learned gate: halo chunks per thread, all in registers: (rows + 2) x 18
+// pixels of up to 64 channels
+constexpr int kLearnItems(int rows, int waves) { return ((rows + 2) * 18 * 8 + waves * 64 - 1) / (waves * 64); }
+
 }  // namespace
 
 using TileKernel = void (*)(GateParams, ConvParams, HaloParams);
@@ -480,7 +485,8 @@ struct TileBuild {
   TileKernel plain, trans, chain, learned1, learned3, chain1, chain3;  // (chain: norm gates; chain1, chain3: learned)
 };
 
-// the builds of sc_tile_tab.hip
+// the builds of sc_tile_tab.hip and sc_tile_parts.hip
 const TileBuild* tile_tab_builds(int* count);
+const TileBuild* tile_parts_builds(int* count);
 
 }  // namespace sc

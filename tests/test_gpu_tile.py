@@ -177,7 +177,9 @@ def test_tile_kernel_learned_gate(case, stats):
 # (n, h, w, c_in, c_out, k, block, dtype, learned)
 CHAIN = [(1, 181, 187, 64, 64, 3, 8, "bf16", False), (3, 170, 171, 64, 32, 3, 16, "bf16", False), (1, 60, 75, 48, 80, 3, 4, "bf16", False),
          (1, 60, 51, 136, 20, 1, 2, "bf16", False), (1, 181, 187, 64, 64, 3, 8, "bf16", True), (1, 190, 181, 32, 32, 1, 4, "bf16", True),
-         (1, 40, 52, 64, 64, 3, 8, "f32", False), (1, 30, 41, 40, 128, 3, 1, "f32", False)]
+         (1, 40, 52, 64, 64, 3, 8, "f32", False), (1, 30, 41, 40, 128, 3, 1, "f32", False),
+         # the short-chain builds of two and eight column tiles
+         (1, 150, 141, 32, 32, 3, 8, "bf16", False), (1, 150, 141, 64, 128, 3, 4, "bf16", True)]
 
 
 @pytest.mark.parametrize("case", CHAIN, ids=["x".join(map(str, c)) for c in CHAIN])
@@ -205,3 +207,37 @@ def test_chained_step_is_the_plain_step_bit_for_bit(case):
         assert np.array_equal(one.stat().view(np.uint32), two.stat().view(np.uint32))
     for layer in (up, one, two):
         layer.close()
+
+
+def _distance(layer, frames, wt, k, s, dtype):
+    """Relative 2-norm distance of z after two steps from the exact sums of the same operands (eps = 0: every site on)."""
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    for f in frames:
+        z = layer.step(f.cuda())
+    torch.cuda.synchronize()
+    x = [f.double().permute(0, 3, 1, 2) for f in frames]
+    r = (frames[1].float() - frames[0].float()).to(dt).double().permute(0, 3, 1, 2)
+    conv = lambda a: torch.nn.functional.conv2d(a, wt.double(), stride=s, padding=(k - 1) // 2)  # noqa: E731
+    exact = (conv(x[0]) + conv(r)).permute(0, 2, 3, 1)
+    return float((z.cpu().double() - exact).norm() / exact.norm())
+
+
+# (c_in, c_out, k, stride): layers whose kernel on small frames, with K split over waves, gives way to the tile kernel
+@pytest.mark.parametrize("case", [(64, 64, 3, 1), (32, 64, 3, 1), (32, 32, 3, 1), (64, 32, 3, 1), (64, 96, 3, 1)],
+                         ids=lambda c: "x".join(map(str, c)))
+def test_tile_kernel_is_as_exact_as_the_register_operand_kernel(case):
+    """The distance from the exact sums does not grow where the tile kernel takes over. The frames of both sizes have the
+    same distribution, so the distances are two measurements of one figure over >= 130,000 outputs each, which scatter
+    by less than 1 %; one accumulator chain over K instead of partial sums is 1.4 to 1.75 times as far."""
+    ci, co, k, s = case
+    g = torch.Generator().manual_seed(17 + ci + co)
+    wt = (torch.randn(co, ci, k, k, generator=g) * (2.0 / (k * k * ci)) ** 0.5).bfloat16()
+    got = []
+    for h, w in ((64, 64), (200, 200)):
+        frames = [torch.rand(1, h, w, ci, generator=g).bfloat16() for _ in range(2)]
+        layer = S.SkipConv(wt.cuda(), n=1, h=h, w=w, stride=s, eps=0.0, block=8)
+        got.append((layer.fused_variant, _distance(layer, frames, wt, k, s, "bf16")))
+        layer.close()
+    say(f"[tile distance {case}] {got}")
+    assert got[0][0] in (2, 3) and got[1][0] == 6
+    assert got[1][1] <= 1.03 * got[0][1], got
