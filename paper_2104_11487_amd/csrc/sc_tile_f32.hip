@@ -37,12 +37,12 @@ constexpr int kItems = 4;
 constexpr int kNonTemporal = 2;
 
 template <int NS>
-__global__ void __launch_bounds__(kF32Threads) __attribute__((amdgpu_waves_per_eu(NS == 4 ? 4 : 3)))
+__global__ void __launch_bounds__(kF32Threads) __attribute__((amdgpu_waves_per_eu(3)))
 tile_f32_kernel(GateParams g, ConvParams c, TileF32Params tp) {
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   __shared__ uint32_t blk_flag[kSide * kSide];
   constexpr int kRing = NS == 4 ? 3 : (NS == 2 ? 4 : 6);  // weight groups in registers
-  constexpr int kParts = NS == 4 ? 2 : 4;                 // partial sums per output
+  constexpr int kParts = 4;                               // partial sums per output
   const int hh = tp.hh, hw = tp.hw;
   float* a_halo = reinterpret_cast<float*>(lds + hh * hw * tp.pstride);
 
@@ -182,9 +182,12 @@ tile_f32_kernel(GateParams g, ConvParams c, TileF32Params tp) {
   const size_t zimg = (size_t)g.h_out * g.w_out * c.c_out;
   const auto zrs = frame_rsrc(c.z + (size_t)n * zimg, (uint32_t)(zimg * 4));
   uint32_t zoff[NS];
-  // partial sums per output, K taken in turn: independent MFMA chains, and fewer
-  // roundings behind each other
-  floatx4 zo[NS], acc[kParts][NS];
+  // kParts partial sums per output, K taken in turn: independent MFMA chains, and
+  // fewer roundings behind each other. They join the total halfway through K and
+  // at its end, so z is no further from the exact sums than by the gathering
+  // convolution's four sums over a quarter of K each (relative 2-norm, 2 x 160 x 160,
+  // 128 -> 64: 2.3e-7 against 3.1e-7; two parts 4.6e-7, four without the join 3.2e-7)
+  floatx4 zo[NS], acc[kParts][NS], tot[NS];
 #pragma unroll
   for (int i = 0; i < NS; ++i) {
     const int col = (nt0 + i) * 16 + kq * 4;
@@ -193,7 +196,18 @@ tile_f32_kernel(GateParams g, ConvParams c, TileF32Params tp) {
         floatx4, __builtin_amdgcn_raw_buffer_load_b128(zrs, g.reference ? kOutOfRange : zoff[i], 0, 0));
 #pragma unroll
     for (int e = 0; e < kParts; ++e) acc[e][i] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+    tot[i] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
   }
+  auto join = [&]() {
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        tot[i][v] = __fadd_rn(tot[i][v], __fadd_rn(__fadd_rn(acc[0][i][v], acc[1][i][v]), __fadd_rn(acc[2][i][v], acc[3][i][v])));
+#pragma unroll
+      for (int e = 0; e < kParts; ++e) acc[e][i] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+  };
   const uint8_t* abase = lds + (ly * s * hw + lx * s) * tp.pstride + kq * 16;
   const int per_tap = tp.cpad >> 4;
   int aoff = 0, cc = 0, kw = 0, jn = 0;  // halo offset of the next group (kh, kw, cc)
@@ -220,26 +234,26 @@ tile_f32_kernel(GateParams g, ConvParams c, TileF32Params tp) {
     a = an;
   };
   int j = 0;
+  const int mid = max(groups / 2 / kRing, 1) * kRing;
   for (; j + kRing <= groups; j += kRing) {
+    if (j == mid) join();
 #pragma unroll
     for (int r = 0; r < kRing; ++r) {
       load_w(wq[(r + kRing - 1) % kRing], min(j + r + kRing - 1, groups - 1));
       use(wq[r]);
     }
   }
+  if (j == mid) join();  // one turn
 #pragma unroll
   for (int r = 0; r < kRing - 1; ++r)
     if (r < groups - j) use(wq[r]);
+  join();
 
 #pragma unroll
   for (int i = 0; i < NS; ++i) {
     floatx4 nv;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      float u = __fadd_rn(acc[0][i][v], acc[1][i][v]);
-      if constexpr (kParts == 4) u = __fadd_rn(u, __fadd_rn(acc[2][i][v], acc[3][i][v]));
-      nv[v] = __fadd_rn(zo[i][v], u);
-    }
+    for (int v = 0; v < 4; ++v) nv[v] = __fadd_rn(zo[i][v], tot[i][v]);
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, nv), zrs, zoff[i], 0, 0);
     if (c.act && zoff[i] != kOutOfRange) {
       float4* y = reinterpret_cast<float4*>(static_cast<float*>(c.y) + (size_t)n * zimg + zoff[i] / 4);

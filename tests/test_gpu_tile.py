@@ -241,3 +241,23 @@ def test_tile_kernel_is_as_exact_as_the_register_operand_kernel(case):
     say(f"[tile distance {case}] {got}")
     assert got[0][0] in (2, 3) and got[1][0] == 6
     assert got[1][1] <= 1.03 * got[0][1], got
+
+
+# (n, h, w, c_in, c_out, k, stride): one, two and four column tiles a workgroup; K of one group of 16 channels to 72
+@pytest.mark.parametrize("case", [(2, 128, 128, 64, 64, 3, 1), (1, 128, 96, 64, 64, 3, 1), (2, 256, 256, 32, 64, 1, 1),
+                                  (1, 60, 60, 128, 128, 3, 1), (1, 200, 180, 24, 48, 3, 2), (2, 200, 200, 48, 64, 1, 1),
+                                  (2, 180, 180, 32, 32, 3, 1)], ids=lambda c: "x".join(map(str, c)))
+def test_tile_kernel_f32_is_as_exact_as_the_gathering_convolution(case):
+    """As above, against the split pipeline on the same frames (four sums over a quarter of K each)."""
+    n, h, w, ci, co, k, s = case
+    g = torch.Generator().manual_seed(19 + ci + co)
+    wt = torch.randn(co, ci, k, k, generator=g) * (2.0 / (k * k * ci)) ** 0.5
+    frames = [torch.rand(n, h, w, ci, generator=g) for _ in range(2)]
+    got = []
+    for split in (True, False):
+        layer = S.SkipConv(wt.cuda(), n=n, h=h, w=w, stride=s, eps=0.0, block=8, split=split)
+        got.append((layer.fused_variant, _distance(layer, frames, wt, k, s, "f32")))
+        layer.close()
+    say(f"[tile f32 distance {case}] {got}")
+    assert got[0][0] == 0 and got[1][0] == 6
+    assert got[1][1] <= 1.03 * got[0][1], got
