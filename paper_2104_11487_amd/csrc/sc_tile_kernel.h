@@ -311,8 +311,8 @@ tile_kernel(GateParams g, ConvParams c, HaloParams hp) {
       __builtin_amdgcn_raw_buffer_store_b128(
           vt[u], rk, own ? (uint32_t)(((y * g.w + x) * g.c + ch * kChunk) * kE) : kOutOfRange, 0, kNonTemporal);
     });
-    // the taps' sums of a site meet in tap order (an out-of-frame tap's sum is
-    // +0, which adds nothing), then the bias
+    // the taps' sums of a site meet in tap order, then the bias; out-of-frame taps
+    // add +0 (their own sums, zeros times phi, are NaN where phi is not finite)
     if constexpr (kSplit > 1) {
       if (tg > 0) {
 #pragma unroll
@@ -324,7 +324,11 @@ tile_kernel(GateParams g, ConvParams c, HaloParams hp) {
     if (threadIdx.x < kSites && ly < oh && lx < ow) {
       float sv = 0.0f;
 #pragma unroll
-      for (int t = 0; t < K2; ++t) sv = add_rn(sv, t < TPT ? acc[t < TPT ? t : 0] : rbuf[t * kSites + threadIdx.x]);
+      for (int t = 0; t < K2; ++t) {
+        const int y = iy0 + ly * s + t / LEARN, x = ix0 + lx * s + t % LEARN;
+        const float v = t < TPT ? acc[t < TPT ? t : 0] : rbuf[t * kSites + threadIdx.x];
+        sv = add_rn(sv, y >= 0 && y < g.h && x >= 0 && x < g.w ? v : 0.0f);
+      }
       sv = add_rn(sv, g.gate_bias);
       decide(ly, lx, sv, sv > 0.0f);
     }

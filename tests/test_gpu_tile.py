@@ -174,6 +174,30 @@ def test_tile_kernel_learned_gate(case, stats):
     layer.close()
 
 
+@pytest.mark.parametrize("shape", [(1, 37, 50, 32, 8), (1, 181, 187, 64, 64)], ids=["one_column", "four_columns"])
+@pytest.mark.parametrize("tap,value", [((0, 0), np.inf), ((2, 2), np.nan), ((1, 0), -np.inf)])
+def test_tile_kernel_learned_gate_leaves_out_of_frame_taps_out(shape, tap, value):
+    """A gate weight that is not finite decides at the sites whose tap lies in the frame and at no other: along the
+    border where it does not, the score is the sum of the other taps."""
+    n, h, w, ci, co = shape
+    rng = np.random.Generator(np.random.PCG64(78))
+    frames = list(syn.RectVideo(h, w, ci, 3, seed=79, batch=n, n_rect=2, side_lo=5, side_hi=12))
+    wt = rng.normal(0, 0.15, (co, ci, 3, 3)).astype(np.float32)
+    phi = rng.normal(0, 0.05, (ci, 3, 3)).astype(np.float32)
+    phi[5][tap] = value
+    layer, orc = _layer_pair(wt, n=n, h=h, w=w, dtype="bf16", eps=0.0, block=1, gate="learned", phi=phi, gate_bias=-0.25)
+    assert layer.fused_variant == 6
+    for t, f in enumerate(frames):
+        xs = syn.to_storage(f, "bf16")
+        say(f"[tile learned {shape} {tap} {value}] frame {t}")
+        layer.step(to_device(xs, "bf16"))
+        ref = orc.step(xs)
+        compare_frame(layer, ref, "bf16", t=t, tag=f"tile learned {tap} {value}", keep_stats=True)
+        edge = ref["site_mask"][:, {0: 0, 2: -1}.get(tap[0], slice(None)), {0: 0, 2: -1}.get(tap[1], slice(None))]
+        assert t == 0 or not edge.all(), "the border's sites are not decided by the other taps"
+    layer.close()
+
+
 # (n, h, w, c_in, c_out, k, block, dtype, learned)
 CHAIN = [(1, 181, 187, 64, 64, 3, 8, "bf16", False), (3, 170, 171, 64, 32, 3, 16, "bf16", False), (1, 60, 75, 48, 80, 3, 4, "bf16", False),
          (1, 60, 51, 136, 20, 1, 2, "bf16", False), (1, 181, 187, 64, 64, 3, 8, "bf16", True), (1, 190, 181, 32, 32, 1, 4, "bf16", True),
