@@ -136,4 +136,36 @@ __device__ __forceinline__ int xcd_deal(int b, int g) {
   return (i / G * 8 + (b & 7)) * G + i % G;
 }
 
+// Chained steps with a norm gate: the residual is zero outside the upstream
+// layer's active blocks, so a tile whose input region meets none of them has a
+// zero statistic and every gate off. Then true (uniform over the workgroup), with
+// the tile's statistics and block flags written by the threads of `lead`. A tile
+// has oh x ow sites at (oy0, ox0), its rows 1 << lw sites wide and `sites` in all
+// when it is whole; its halo starts at (iy0, ix0). No more sites than threads.
+template <typename G>
+__device__ __forceinline__ bool quiet_tile(const G& g, int n, int iy0, int ix0, int oy0, int ox0, int oh, int ow, int lw,
+                                           int sites, int threads, bool lead) {
+  const int y0 = max(iy0, 0), y1 = min(iy0 + (oh - 1) * g.stride + g.k, g.h);
+  const int x0 = max(ix0, 0), x1 = min(ix0 + (ow - 1) * g.stride + g.k, g.w);
+  const int by0 = y0 / g.up_block, bx0 = x0 / g.up_block;
+  const int nbx = (x1 - 1) / g.up_block - bx0 + 1, cnt = ((y1 - 1) / g.up_block - by0 + 1) * nbx;
+  int any = 0;
+  for (int i = threadIdx.x; i < cnt; i += threads)
+    any |= g.up_mask[((size_t)n * g.up_hb + by0 + i / nbx) * g.up_wb + bx0 + i % nbx] != 0;
+  if (__syncthreads_or(any)) return false;
+  if (!lead) return true;
+  if (g.keep_stats && threadIdx.x < sites) {
+    const int ly = threadIdx.x >> lw, lx = threadIdx.x & ((1 << lw) - 1);
+    const size_t o = ((size_t)n * g.h_out + oy0 + ly) * g.w_out + ox0 + lx;
+    if (ly < oh && lx < ow) {
+      g.stat[o] = 0.0f;
+      g.site_mask[o] = 0;
+    }
+  }
+  const int lblk = __ffs(g.block) - 1, nb = 1 << (lw - lblk), by = threadIdx.x / nb, bx = threadIdx.x - by * nb;
+  if ((by << lblk) < oh && (bx << lblk) < ow)
+    g.block_mask[((size_t)n * g.hb + (oy0 >> lblk) + by) * g.wb + (ox0 >> lblk) + bx] = 0;
+  return true;
+}
+
 }  // namespace sc

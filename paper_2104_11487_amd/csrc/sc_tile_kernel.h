@@ -99,29 +99,7 @@ tile_kernel(GateParams g, ConvParams c, HaloParams hp) {
   if (threadIdx.x < kMaxTileBlocks) blk_flag[threadIdx.x] = 0u;
 
   if constexpr (CHAIN && !LEARN) {
-    // the residual is zero outside the upstream layer's active blocks: a tile
-    // whose input region meets none of them has every gate off
-    const int y0 = max(iy0, 0), y1 = min(iy0 + (oh - 1) * s + k, g.h);
-    const int x0 = max(ix0, 0), x1 = min(ix0 + (ow - 1) * s + k, g.w);
-    const int by0 = y0 / g.up_block, bx0 = x0 / g.up_block;
-    const int nbx = (x1 - 1) / g.up_block - bx0 + 1, cnt = ((y1 - 1) / g.up_block - by0 + 1) * nbx;
-    int any = 0;
-    for (int i = threadIdx.x; i < cnt; i += kTileThreads)
-      any |= g.up_mask[((size_t)n * g.up_hb + by0 + i / nbx) * g.up_wb + bx0 + i % nbx] != 0;
-    if (!__syncthreads_or(any)) {
-      if (g.keep_stats && threadIdx.x < th * tw) {
-        const int ly = threadIdx.x >> lw, lx = threadIdx.x & (tw - 1);
-        const size_t o = ((size_t)n * g.h_out + oy0 + ly) * g.w_out + ox0 + lx;
-        if (ly < oh && lx < ow) {
-          g.stat[o] = 0.0f;
-          g.site_mask[o] = 0;
-        }
-      }
-      const int nb = tw >> lblk, by = threadIdx.x / nb, bx = threadIdx.x - by * nb;
-      if ((by << lblk) < oh && (bx << lblk) < ow)
-        g.block_mask[((size_t)n * g.hb + (oy0 >> lblk) + by) * g.wb + (ox0 >> lblk) + bx] = 0;
-      return;
-    }
+    if (g.up_mask && quiet_tile(g, n, iy0, ix0, oy0, ox0, oh, ow, lw, th * tw, kTileThreads, true)) return;
   }
 
   // ---- halo ----

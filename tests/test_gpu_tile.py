@@ -233,6 +233,43 @@ def test_chained_step_is_the_plain_step_bit_for_bit(case):
         layer.close()
 
 
+def test_chained_f32_tiles_without_upstream_blocks_load_nothing():
+    """No site is on in either step (eps is huge), so they differ in the loads alone: nothing changed upstream, or
+    everything did (67 MB of residual, read by each of a tile's two shares). 10 against 40 us; 35 both if every tile loads."""
+    g = torch.Generator().manual_seed(31)
+    n, h, w, ci, co = 2, 256, 256, 128, 128
+    up = S.SkipConv(torch.randn(ci, 8, 1, 1, generator=g).cuda(), n=n, h=h, w=w, eps=0.0, block=8, act_out="relu", emit_residual=True)
+    one = S.SkipConv(torch.randn(co, ci, 3, 3, generator=g).cuda(), n=n, h=h, w=w, eps=1e9, block=8)
+    assert one.fused_variant == 6
+    x = torch.rand(n, h, w, 8, generator=g).cuda()
+    up.step(x)
+    one.step_chained(up)  # the reference frame
+
+    def us():
+        best = float("inf")
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                one.step_chained(up)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) / 20 * 1e3)
+        return best
+
+    for f in (x.clone(), x.clone()):
+        up.step(f)
+    assert not up.block_mask().any()
+    quiet = us()
+    up.step(x + 1)
+    assert up.block_mask().all()
+    busy = us()
+    say(f"[tile f32 chained] quiet {quiet:.1f} us, all changed {busy:.1f} us")
+    assert quiet < 0.75 * busy, (quiet, busy)
+    up.close()
+    one.close()
+
+
 def _distance(layer, frames, wt, k, s, dtype):
     """Relative 2-norm distance of z after two steps from the exact sums of the same operands (eps = 0: every site on)."""
     dt = torch.float32 if dtype == "f32" else torch.bfloat16
