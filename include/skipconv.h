@@ -231,7 +231,7 @@ int skipconv_step_translated(skipconv_t h, const void* x_t, int32_t dy, int32_t 
  * must have stepped the same frame already on `stream` (stream order).
  * Instead of reading x_t and x_{t-1} over the whole frame, the gate reads
  * `up`'s residual, and gate tiles whose input region holds no active block of
- * `up` skip their loads (norm gates); the convolution reads the residual
+ * `up` skip their loads (norm gates without FORCE_DENSE); the convolution reads the residual
  * operand. Masks, counts and z are exactly those that skipconv_step with
  * x_t = dtype(act(z_up)) would give. A reference frame of this layer reads
  * `up`'s activation output in full. This layer's own x_{t-1} slots are not

@@ -1358,6 +1358,9 @@ int skipconv_step_chained(skipconv_t h, skipconv_t up, void* stream, const float
   const skipconv_desc& d = h->d;
   const Geometry& g = h->g;
   const bool bf16 = d.dtype == SKIPCONV_BF16;
+  // a zero residual leaves a norm gate off, so tiles without upstream blocks
+  // skip; with FORCE_DENSE every block is active, as in a plain step
+  const bool skip_quiet = !g.learned && !(d.flags & SKIPCONV_FLAG_FORCE_DENSE);
   if (g.fused) {
     // one-pass kernel on the fp32 residual (it rounds the operand itself)
     sc::FusedParams fp = fused_params(h, up->r32(), false);
@@ -1365,7 +1368,7 @@ int skipconv_step_chained(skipconv_t h, skipconv_t up, void* stream, const float
     fp.g.x_keep = nullptr;
     fp.g.no_prev = 1;
     fp.g.rin = 1;
-    if (!g.learned) {
+    if (skip_quiet) {
       fp.g.up_mask = up->bmask();
       fp.g.up_block = up->d.block;
       fp.g.up_hb = up->g.hb;
@@ -1384,7 +1387,7 @@ int skipconv_step_chained(skipconv_t h, skipconv_t up, void* stream, const float
   gp.x_prev = nullptr;
   gp.x_keep = nullptr;
   gp.no_prev = 1;
-  if (!g.learned) {  // a zero residual leaves a norm gate off: tiles without upstream blocks skip
+  if (skip_quiet) {
     gp.up_mask = up->bmask();
     gp.up_block = up->d.block;
     gp.up_hb = up->g.hb;

@@ -233,6 +233,38 @@ def test_chained_step_is_the_plain_step_bit_for_bit(case):
         layer.close()
 
 
+# tile kernel (bf16, chunk table, fp32), split pipeline, single-pass kernel with LDS and with register weights, few channels
+DENSE_CHAIN = [((1, 181, 187, 64, 64, 3, 8, "bf16", False), 6), ((1, 60, 75, 48, 80, 3, 4, "bf16", False), 6),
+               ((1, 40, 52, 64, 64, 3, 8, "f32", False), 6), ((1, 40, 52, 64, 64, 3, 8, "bf16", True), 0),
+               ((1, 40, 52, 64, 64, 3, 8, "f32", True), 0), ((1, 40, 52, 64, 64, 1, 8, "bf16", False), 1),
+               ((1, 40, 52, 64, 64, 3, 8, "bf16", False), 2), ((1, 40, 52, 16, 16, 3, 4, "f32", False), 5)]
+
+
+@pytest.mark.parametrize("case,kind", DENSE_CHAIN, ids=["x".join(map(str, c)) for c, _ in DENSE_CHAIN])
+def test_force_dense_chained_step_has_every_block_on(case, kind):
+    """FORCE_DENSE makes every block active on every frame, also on a chained step after which nothing changed upstream
+    (a tile is not skipped for a quiet input), in every kernel alike; z is that of the gated layer."""
+    n, h, w, ci, co, k, b, dtype, split = case
+    rng = np.random.Generator(np.random.PCG64(51 + k))
+    frames = list(syn.RectVideo(h, w, 8, 3, seed=52, batch=n, n_rect=1, side_lo=5, side_hi=9, noise_std=0.0))
+    frames.append(frames[-1])
+    w0 = to_device(weight_storage(rng.normal(0, 0.3, (ci, 8, 1, 1)).astype(np.float32), dtype), dtype)
+    w1 = to_device(weight_storage(rng.normal(0, 0.1, (co, ci, k, k)).astype(np.float32), dtype), dtype)
+    up = S.SkipConv(w0, n=n, h=h, w=w, eps=0.0, block=b, act_out="relu", emit_residual=True)
+    kw = dict(n=n, h=h, w=w, eps=0.0, block=b, keep_stats=True, split=split)
+    dense, gated = S.SkipConv(w1, force_dense=True, **kw), S.SkipConv(w1, **kw)
+    assert dense.fused_variant == kind
+    for t, f in enumerate(frames):
+        up.step(to_device(syn.to_storage(f, dtype), dtype))
+        za, zb = dense.step_chained(up), gated.step_chained(up)
+        torch.cuda.synchronize()
+        assert dense.block_mask().all() and dense.site_mask().all(), (case, t)
+        assert t == 0 or not gated.block_mask().all()
+        assert torch.equal(za, zb) and np.array_equal(dense.stat(), gated.stat())
+    for layer in (up, dense, gated):
+        layer.close()
+
+
 def test_chained_f32_tiles_without_upstream_blocks_load_nothing():
     """No site is on in either step (eps is huge), so they differ in the loads alone: nothing changed upstream, or
     everything did (67 MB of residual, read by each of a tile's two shares). 10 against 40 us; 35 both if every tile loads."""
