@@ -1096,15 +1096,18 @@ int skipconv_create(const skipconv_desc* d, const void* weights, void* workspace
   // keep the 8 x 8 tiles to three rounds (24 x 24 / 28 x 28 tiles: 32 -> 32 at
   // stride 2 14.9 against 16.2 / 18.9 against 16.7 us), 128 -> 32 and 128 -> 64 to
   // the end (1 x 1 128 -> 64, 31 x 31: 16.6 against 17.0; 128 -> 32, 28 x 28 tiles,
-  // 24.2 against 22.1 us, where one chain over K = 1152 more than doubled the
-  // distance from the exact sums).
+  // 24.2 against 22.1 us), and so does every 3 x 3 layer of 128 channels: one chain
+  // over K = 1152 more than doubles the distance from the exact sums, chains of two
+  // k-steps still add 6 to 14 % (128 -> 96 and 128 -> 128; a step of 100 x 100
+  // 20.4 against 19.0 us, chained, 3 % covered, 12.7 against 20.3, translated 30.5
+  // against 33.4; of 128 x 128 25.5 against 19.8, chained 14.7 against 20.1).
   bool takes_over = false;
   if (h->g.tile && h->g.fused && h->g.f_mw == 1) {
     const long wgs = (long)h->g.f_grid * h->g.f_nsplit;
     const bool early = d->c_in <= 64 && (h->g.ntn >= 8 || (d->stride == 1 && h->g.ksteps <= 9 &&
                                                            (h->g.ntn == 2 || d->kernel == 1)));
     const bool late = d->c_in < 64 && d->stride > 1 && d->kernel > 1;
-    const int rounds = early ? 1 : (d->c_in == 128 && h->g.ntn <= 4) ? 4 : late ? 3 : 2;
+    const int rounds = early ? 1 : (d->c_in == 128 && (h->g.ntn <= 4 || h->g.f_rb)) ? 4 : late ? 3 : 2;
     // the register-operand kernel gives way only to builds as exact as itself
     takes_over = wgs > rounds * (long)h->num_cu && (!h->g.f_rb || h->g.tp.rows == 8);
     h->g.tp.parts = takes_over && h->g.f_rb;

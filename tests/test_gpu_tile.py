@@ -20,7 +20,7 @@ pytestmark = pytest.mark.gpu
 # take the kernel
 CASES = [
     (1, 181, 187, 64, 64, 3, 1, 8, 6), (1, 181, 187, 32, 20, 3, 1, 1, 6), (2, 130, 141, 32, 64, 1, 1, 2, 6),
-    (1, 150, 140, 64, 128, 3, 1, 4, 6), (1, 100, 91, 128, 128, 3, 1, 8, 6), (3, 170, 171, 64, 64, 3, 1, 16, 6),
+    (1, 150, 140, 64, 128, 3, 1, 4, 6), (1, 190, 181, 128, 128, 3, 1, 4, 6), (3, 170, 171, 64, 64, 3, 1, 16, 6),
     (1, 41, 70, 64, 12, 3, 1, 16, 0), (1, 37, 50, 64, 8, 3, 1, 4, 0), (1, 183, 185, 32, 32, 5, 1, 8, 6),
     # channel counts that are no multiple of 32 (chunk table), 8 x 8 tiles, up to 16 column tiles
     (1, 135, 181, 48, 80, 3, 2, 4, 6), (1, 50, 41, 24, 16, 5, 1, 2, 6), (2, 60, 77, 72, 160, 3, 1, 8, 6),
@@ -195,6 +195,21 @@ def test_tile_kernel_learned_gate_leaves_out_of_frame_taps_out(shape, tap, value
         compare_frame(layer, ref, "bf16", t=t, tag=f"tile learned {tap} {value}", keep_stats=True)
         edge = ref["site_mask"][:, {0: 0, 2: -1}.get(tap[0], slice(None)), {0: 0, 2: -1}.get(tap[1], slice(None))]
         assert t == 0 or not edge.all(), "the border's sites are not decided by the other taps"
+    layer.close()
+
+
+# (n, h, w, c_in, c_out, k, stride, block, learned gate, pipeline reported) on both sides of the lines between the kernels
+ROUTES = [
+    (1, 100, 100, 128, 128, 3, 1, 8, False, 3), (1, 128, 128, 128, 96, 3, 1, 4, False, 3),
+]
+
+
+@pytest.mark.parametrize("case", ROUTES, ids=["x".join(map(str, c)) for c in ROUTES])
+def test_layers_run_on_the_kernel_that_is_ahead(case):
+    n, h, w, ci, co, k, s, b, learned, kind = case
+    layer = S.SkipConv(torch.zeros(co, ci, k, k, dtype=torch.bfloat16, device="cuda"), n=n, h=h, w=w, stride=s, block=b,
+                       gate="learned" if learned else "input")
+    assert layer.fused_variant == kind
     layer.close()
 
 
