@@ -1090,6 +1090,8 @@ int skipconv_create(const skipconv_desc* d, const void* weights, void* workspace
   // frame: 17.6 -> 16.3 us; 256 x 256: 23.2 -> 17.4 us), or more than one where
   // the output is wide (138 x 130, 64 -> 96: 15.4 -> 13.2 us) or, at stride 1,
   // the product is short (160 x 160, 32 -> 32 9.0 -> 7.5 us; 1 x 1 64 -> 32 9.0 -> 7.7 us);
+  // (32 -> 128, whose 8 x 8 tiles two workgroups share, two: 160 x 160 15.1 -> 11.5 us,
+  // but 128 x 128 9.2 against 10.6, 100 x 100 8.7 against 10.6);
   // before that they win (64 -> 64, 160 x 160: 12.8 against 13.4 us, 128 x 96:
   // 7.0 against 12 us; 32 -> 64 8.4 against 9.2 us; 32 -> 32 at stride 2, 19 x 19
   // tiles, 10.8 against 14.5 us). Layers with much staging for little product
@@ -1107,7 +1109,7 @@ int skipconv_create(const skipconv_desc* d, const void* weights, void* workspace
     const bool early = d->c_in <= 64 && (h->g.ntn >= 8 || (d->stride == 1 && h->g.ksteps <= 9 &&
                                                            (h->g.ntn == 2 || d->kernel == 1)));
     const bool late = d->c_in < 64 && d->stride > 1 && d->kernel > 1;
-    const int rounds = early ? 1 : (d->c_in == 128 && (h->g.ntn <= 4 || h->g.f_rb)) ? 4 : late ? 3 : 2;
+    const int rounds = early ? (h->g.f_nsplit > 1 ? 2 : 1) : (d->c_in == 128 && (h->g.ntn <= 4 || h->g.f_rb)) ? 4 : late ? 3 : 2;
     // the register-operand kernel gives way only to builds as exact as itself
     takes_over = wgs > rounds * (long)h->num_cu && (!h->g.f_rb || h->g.tp.rows == 8);
     h->g.tp.parts = takes_over && h->g.f_rb;

@@ -201,6 +201,7 @@ def test_tile_kernel_learned_gate_leaves_out_of_frame_taps_out(shape, tap, value
 # (n, h, w, c_in, c_out, k, stride, block, learned gate, pipeline reported) on both sides of the lines between the kernels
 ROUTES = [
     (1, 100, 100, 128, 128, 3, 1, 8, False, 3), (1, 128, 128, 128, 96, 3, 1, 4, False, 3),
+    (1, 128, 128, 32, 128, 3, 1, 8, False, 3), (1, 160, 160, 32, 128, 3, 1, 8, False, 6),
 ]
 
 
