@@ -1110,8 +1110,12 @@ int skipconv_create(const skipconv_desc* d, const void* weights, void* workspace
                                                            (h->g.ntn == 2 || d->kernel == 1)));
     const bool late = d->c_in < 64 && d->stride > 1 && d->kernel > 1;
     const int rounds = early ? (h->g.f_nsplit > 1 ? 2 : 1) : (d->c_in == 128 && (h->g.ntn <= 4 || h->g.f_rb)) ? 4 : late ? 3 : 2;
+    // 96 channels keep a quarter of the tile kernel's lanes idle in the halo: 1 x 1
+    // layers at stride 1 and 96 -> 32 stay (200 x 200, 96 -> 32: 11.0 against 15.5 us,
+    // 3 x 3 20.9 against 22.8; 96 -> 128, 1 x 1, 14.4 against 15.2)
+    const bool stay = h->g.tp.tab_off && d->stride == 1 && (d->kernel == 1 || (h->g.ntn == 2 && d->kernel == 3));
     // the register-operand kernel gives way only to builds as exact as itself
-    takes_over = wgs > rounds * (long)h->num_cu && (!h->g.f_rb || h->g.tp.rows == 8);
+    takes_over = wgs > rounds * (long)h->num_cu && !stay && (!h->g.f_rb || h->g.tp.rows == 8);
     h->g.tp.parts = takes_over && h->g.f_rb;
   }
   if (h->g.tile && (d->dtype == SKIPCONV_F32 ? sc::tile_f32_occupancy(h->g.tf)

@@ -202,6 +202,7 @@ def test_tile_kernel_learned_gate_leaves_out_of_frame_taps_out(shape, tap, value
 ROUTES = [
     (1, 100, 100, 128, 128, 3, 1, 8, False, 3), (1, 128, 128, 128, 96, 3, 1, 4, False, 3),
     (1, 128, 128, 32, 128, 3, 1, 8, False, 3), (1, 160, 160, 32, 128, 3, 1, 8, False, 6),
+    (1, 200, 200, 96, 32, 3, 1, 8, False, 1), (1, 200, 200, 96, 128, 1, 1, 8, False, 1), (1, 200, 200, 96, 96, 3, 1, 8, False, 6),
 ]
 
 
