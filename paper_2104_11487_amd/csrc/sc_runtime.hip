@@ -56,8 +56,9 @@ struct Geometry {
   sc::HaloParams hp;
   bool dw_halo;         // depthwise bf16: residual halo of tr x b sites in LDS
   sc::HaloParams dwp;
-  bool tile;            // one-launch tile kernel: reference frames and translated steps
-  bool tile_plain;      // ... and plain steps
+  bool tile;            // one-launch tile kernel: translated steps
+  bool tile_ref;        // ... reference frames
+  bool tile_plain;      // ... and plain and chained steps
   sc::HaloParams tp;
   sc::TileF32Params tf;  // fp32 layers (tp unused): their tile kernel
   int t_tiles_y, t_tiles_x, t_copy_in_halo;
@@ -330,7 +331,7 @@ int derive(const skipconv_desc* d, Geometry* g, char* err) {
 
   // one-launch tile kernel (no emission, whole 8-channel chunks): tiles of 16 x
   // 16, 8 x 16 or (C_in % 32 != 0) 8 x 8 sites
-  G.tile = G.tile_plain = false;
+  G.tile = G.tile_ref = G.tile_plain = false;
   if (!depthwise && d->dtype == SKIPCONV_BF16 && d->c_in % 8 == 0 && d->c_in >= 16 && d->c_in <= 256 &&
       (d->c_in <= 128 || d->c_in % 32) && d->c_out % 4 == 0 && (b & (b - 1)) == 0 && b <= 16 &&
       !(d->flags & (SKIPCONV_FLAG_SPLIT_PIPELINE | SKIPCONV_FLAG_EMIT_RESIDUAL | SKIPCONV_FLAG_LARGE_GATE_TILES)) &&
@@ -360,6 +361,11 @@ int derive(const skipconv_desc* d, Geometry* g, char* err) {
                          halo_covers_owned(d->w, G.w_out, H.side, G.t_tiles_x, s, pad, k);
       G.tile = true;
     }
+    // reference frames: where the block-halo convolution takes whole 16 x 16
+    // blocks, it is ahead on many tiles of 128 output channels, whose tile build
+    // has two waves per SIMD (64 -> 128, 400 x 400: 49.3 against 55.5 us, 2 x 512 x
+    // 512 146 against 171, 320 x 320 40.1 against 38.5)
+    G.tile_ref = G.tile && !(b > 8 && d->c_in <= 64 && G.ntn >= 8 && tiles16 > 2 * kCuGuess);
     // plain steps: few tiles per CU, where two kernels are mostly latency, and
     // blocks smaller than 8, whose other convolution gathers site by site.
     // Measured (tile / split, us): 64 -> 64, 16 x 16 blocks, 2 x 256 x 256
@@ -386,6 +392,7 @@ int derive(const skipconv_desc* d, Geometry* g, char* err) {
     G.t_tiles_x = (G.w_out + 7) / 8;
     const long tiles = (long)d->n * G.t_tiles_y * G.t_tiles_x;
     G.tile = sc::tile_f32_shape(G.tf, d->c_in, k, s, G.ntn, tiles, kCuGuess, kFusedLdsLimit);
+    G.tile_ref = G.tile;
     // (per-site gates on larger frames of 128 output channels: a whole tile's
     // product for a few sites; 256 x 256, 128 -> 128, 7 % of the sites: 75 us
     // against 64 by the gathering convolution)
@@ -1120,12 +1127,12 @@ int skipconv_create(const skipconv_desc* d, const void* weights, void* workspace
   }
   if (h->g.tile && (d->dtype == SKIPCONV_F32 ? sc::tile_f32_occupancy(h->g.tf)
                                              : sc::tile_occupancy(h->g.tp, h->g.ntn, h->g.ksteps)) < 1)
-    h->g.tile = h->g.tile_plain = takes_over = false;
+    h->g.tile = h->g.tile_ref = h->g.tile_plain = takes_over = false;
   if (takes_over) {
     h->g.fused = false;
     h->g.tile_plain = true;
   } else if (h->g.fused) {
-    h->g.tile = h->g.tile_plain = false;
+    h->g.tile = h->g.tile_ref = h->g.tile_plain = false;
   }
   h->conv_occ = conv_setup(h->g, d, h->device);
   if (workspace) {
@@ -1206,7 +1213,7 @@ int skipconv_step(skipconv_t h, const void* x_t, void* stream, const float** z_t
 
   hipError_t e = hipSuccess;
   if (timing) e = hipEventRecord(h->ev[3 * h->timing_done], st);
-  if (g.tile_plain || (g.tile && ref)) {
+  if (g.tile_plain || (g.tile_ref && ref)) {
     if (e == hipSuccess) e = launch_tile(h, gp, cp, st);
     if (e != hipSuccess) return hip_fail(h, e, "tile launch");
     if (timing) e = hipEventRecord(h->ev[3 * h->timing_done + 1], st);
