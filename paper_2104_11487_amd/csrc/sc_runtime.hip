@@ -373,6 +373,24 @@ int derive(const skipconv_desc* d, Geometry* g, char* err) {
     // 128 channels on either side 2 x 256 x 256 33.5 / 30.6 and 55 / 46.
     // The learned gate is VALU work, so its tiles gain at every size, and so do
     // channel counts whose other convolution gathers site by site.
+    // (They gain by the product. Where that is short and the halo pass wastes what
+    // it has, the gate kernel of the split pipeline is ahead on many tiles: 1 x 1
+    // layers of which a pixel's chunks fill less than 4/5 of their lane group, more
+    // than four tiles per CU, or two where the build has two waves per SIMD or
+    // its LDS leaves a CU few waves (3 % covered: 48 -> 80, 400 x 400, 24.6 against
+    // 31.3 us, 2 x 512 x 512 45.9 against 75.4; 136 -> 40, 2 x 300 x 300, 51.5 against
+    // 60.6; 104 -> 152, whose chunks fill 13 of 16 lanes, 400 x 400, 53.0 -> 48.0), and
+    // strides with more than 128 channels, one workgroup of four waves on a CU, more
+    // than two 8 x 8 tiles per CU (136 -> 40, 2 x 512 x 512: 192 against 389 us;
+    // 300 x 300, 361 tiles, 84 -> 65).)
+    const bool wasteful = (d->c_in >> 3) * 5 < 4 << H.lg_group && d->c_in > 32;
+    const long tiles8 = (long)d->n * ((G.h_out + 7) / 8) * ((G.w_out + 7) / 8);
+    const bool four_waves = d->c_in > 128 && G.ntn <= 4;
+    const bool gate_bound =
+        (k == 1 && s == 1 && wasteful &&
+         (tiles16 > 4 * kCuGuess || (tiles16 >= 2 * kCuGuess && (G.ntn == 8 || four_waves)) ||
+          (four_waves && b > 8 && tiles16 > kCuGuess))) ||
+        (s > 1 && four_waves && tiles8 > 2 * kCuGuess);
     // 128 input channels with blocks smaller than 8 gain with every output width
     // from a workgroup per CU on (128 -> 128, 192 x 192: 24.9 -> 21.3 us; 152 x 152:
     // 19.5 against 20.6 us;
@@ -384,7 +402,7 @@ int derive(const skipconv_desc* d, Geometry* g, char* err) {
     // 25.1 against 33.0 us, 2 x 512 x 512 57.9 against 69.3; 3 x 3, 16 x 16 blocks 39.4
     // against 51.0; 320 x 320, 8 x 16 tiles, 23.6 against 21.5.)
     const bool learned = G.learned && !(G.ntn >= 8 && H.rows == 16 && (k == 1 || b > 8) && tiles16 > 3 * kCuGuess / 2);
-    G.tile_plain = G.tile && (learned || mixed || (!mixed && d->c_in <= 64 && (G.ntn == 2 || G.ntn == 4) &&
+    G.tile_plain = G.tile && (learned || (mixed && !gate_bound) || (!mixed && d->c_in <= 64 && (G.ntn == 2 || G.ntn == 4) &&
                                                      (tiles16 <= 2 * kCuGuess || b < 8)) ||
                               (b < 8 && d->c_in == 128 && G.ntn >= 2 && 2 * tiles16 > kCuGuess));
   }

@@ -28,7 +28,7 @@ CASES = [
     (3, 290, 310, 16, 28, 3, 1, 8, 6), (1, 140, 170, 48, 132, 3, 1, 8, 6),
     (1, 64, 75, 136, 40, 3, 1, 8, 6), (1, 70, 66, 144, 60, 5, 2, 8, 6), (1, 60, 51, 248, 20, 3, 1, 4, 6),
     (1, 190, 185, 96, 96, 3, 1, 8, 6), (1, 75, 90, 48, 32, 1, 2, 4, 6), (1, 270, 271, 128, 32, 3, 1, 1, 6), (3, 290, 350, 32, 64, 1, 2, 8, 6),
-    (1, 281, 290, 32, 100, 3, 2, 4, 6), (9, 160, 240, 32, 40, 3, 1, 8, 0), (5, 250, 243, 32, 100, 1, 1, 16, 0),
+    (1, 281, 290, 32, 100, 3, 2, 4, 6), (9, 160, 240, 32, 40, 3, 1, 8, 0), (5, 250, 243, 32, 100, 1, 1, 16, 0), (1, 260, 270, 136, 40, 1, 1, 16, 0),
 ]
 
 
@@ -204,6 +204,7 @@ ROUTES = [
     (1, 128, 128, 32, 128, 3, 1, 8, False, 3), (1, 160, 160, 32, 128, 3, 1, 8, False, 6),
     (1, 200, 200, 96, 32, 3, 1, 8, False, 1), (1, 200, 200, 96, 128, 1, 1, 8, False, 1), (1, 200, 200, 96, 96, 3, 1, 8, False, 6),
     (1, 400, 400, 64, 128, 1, 1, 8, True, 0), (1, 400, 400, 32, 128, 3, 1, 16, True, 0), (1, 400, 400, 64, 128, 3, 1, 8, True, 6),
+    (1, 400, 400, 48, 80, 1, 1, 8, False, 0), (2, 300, 300, 200, 64, 3, 2, 4, False, 0), (1, 400, 400, 104, 152, 1, 1, 8, False, 6),
 ]
 
 
