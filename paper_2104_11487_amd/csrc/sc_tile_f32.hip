@@ -7,7 +7,7 @@
 // channels of a tile are split over several workgroups, each with NS 16-column
 // tiles: all of them load the halo and evaluate the gate, the first writes what
 // every one would write alike (x_{t-1} copy, statistics, block flags). NS is
-// the largest that still leaves two workgroups per CU.
+// the largest that still leaves two workgroups per CU (one where no more fit).
 //
 //   1. halo: 8-channel chunks (two 16-byte words of each frame), KI in flight
 //      per thread; r = x_t - x_{t-1} to LDS in fp32, the canonical statistic of
@@ -297,7 +297,11 @@ bool tile_f32_shape(TileF32Params& t, int c, int k, int stride, int ntn, long ti
   t.lg_group = 2;
   while (c >> 3 > 1 << t.lg_group || t.cpad >> 3 > 1 << t.lg_group) ++t.lg_group;
   t.ns = ntn < 4 ? ntn : 4;
-  while (t.ns > 1 && tiles * (ntn / t.ns) < 2L * num_cu) t.ns >>= 1;
+  // two workgroups per CU, or the one whose halo fits (128 channels at stride 2:
+  // shares past the first round only load the halo again; 160 x 160, 128 -> 128,
+  // reference 76.0 -> 48.7 us, 30 % covered 62.8 -> 49.3; 200 x 200, 128 -> 64, 60.4 -> 49.9)
+  const long per_cu = lds_of(t) > lds_limit / 2 ? 1 : 2;
+  while (t.ns > 1 && tiles * (ntn / t.ns) < per_cu * num_cu) t.ns >>= 1;
   t.shares = ntn / t.ns;
   t.deal = tiles >= num_cu;
   return lds_of(t) <= lds_limit;
