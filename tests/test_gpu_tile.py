@@ -32,6 +32,22 @@ CASES = [
 ]
 
 
+def _check_off_blocks(expected, layer, mask, b):
+    """The state of the blocks that are off is `expected` there, bit for bit."""
+    n, ho, wo, _ = layer._z.shape
+    on = mask.astype(bool).reshape(n, -(-ho // b), -(-wo // b)).repeat(b, 1).repeat(b, 2)[:, :ho, :wo]
+    off = torch.from_numpy(~on).cuda()
+    assert torch.equal(layer._z[off].view(torch.int32), expected[off].view(torch.int32)), "an off block's state changed"
+
+
+def _moved(z, dy, dx):
+    """z[y - dy, x - dx], zero outside."""
+    out = torch.zeros_like(z)
+    h, w = z.shape[1:3]
+    out[:, max(0, dy):h + min(0, dy), max(0, dx):w + min(0, dx)] = z[:, max(0, -dy):h - max(0, dy), max(0, -dx):w - max(0, dx)]
+    return out
+
+
 @pytest.mark.parametrize("caller", [False, True], ids=["copy", "retains"])
 @pytest.mark.parametrize("case", CASES, ids=["x".join(map(str, c)) for c in CASES])
 def test_tile_kernel(case, caller):
@@ -60,9 +76,12 @@ def test_tile_kernel(case, caller):
             orc.reset()
         xs = syn.to_storage(f, "bf16")
         say(f"[tile {case}] frame {t} shift={d} eps={eps:.4g}")
+        before = layer._z.clone() if t else None
         layer.step_translated(to_device(xs, "bf16"), *d)
         ref = orc.step(xs, shift=d)
         compare_frame(layer, ref, "bf16", t=t, tag=f"tile {case}", keep_stats=not big)
+        if t not in (0, 3):
+            _check_off_blocks(_moved(before, d[0] // s, d[1] // s), layer, ref["block_mask"], b)
         z = layer._z.cpu().numpy()
         y = layer.activation().view(torch.int16).cpu().numpy().view(np.uint16).reshape(z.shape)
         assert np.array_equal(y, O.f32_to_bf16_rne(np.maximum(z, 0.0).astype(np.float32))), (case, t)
@@ -319,6 +338,57 @@ def test_chained_f32_tiles_without_upstream_blocks_load_nothing():
     assert quiet < 0.75 * busy, (quiet, busy)
     up.close()
     one.close()
+
+
+# Options of the gate and of the frames: (dtype, n, h, w, c_in, c_out, k, stride, block, options). The fp32 and chunk-table
+# kernels are taken from the smallest frames on, the 32-, 64- and 128-channel builds from where the first tests reach them.
+MODES = [("f32", 1, 40, 41, 24, 32, 3, 1, 4), ("bf16", 1, 40, 41, 48, 32, 3, 1, 4), ("bf16", 1, 185, 184, 64, 64, 3, 1, 8),
+         ("bf16", 1, 190, 181, 128, 40, 3, 1, 2)]
+OPTS = [dict(norm_p=1), dict(support="centre"), dict(norm_p=1, support="centre", keep_stats=False), dict(gate="output"),
+        dict(gate="output", norm_p=1, pad=0), dict(pad=2), dict(pad=0, support="centre"), dict(force_dense=True),
+        dict(caller_retains=True), dict(caller_retains=True, keep_stats=False, act_out="relu")]
+STRIDED = [("f32", 1, 65, 73, 32, 24, 3, 3, 2, dict()), ("f32", 1, 65, 73, 24, 24, 3, 4, 4, dict(caller_retains=True)),
+           ("f32", 1, 65, 73, 32, 24, 3, 4, 1, dict(norm_p=1, pad=2)), ("f32", 1, 50, 60, 24, 32, 1, 3, 4, dict(keep_stats=False)),
+           ("bf16", 1, 65, 73, 48, 24, 3, 3, 2, dict(pad=0)), ("bf16", 1, 65, 73, 40, 24, 3, 4, 4, dict()),
+           ("bf16", 1, 65, 73, 24, 24, 5, 4, 1, dict(pad=4, norm_p=1)), ("bf16", 1, 50, 60, 104, 32, 1, 3, 4, dict(gate="output"))]
+
+
+@pytest.mark.parametrize("case", [m + (o,) for m in MODES for o in OPTS] + STRIDED,
+                         ids=lambda c: "x".join(map(str, c[:-1])) + "-" + "-".join(f"{a}_{b}" for a, b in c[-1].items()))
+def test_tile_kernel_options(case):
+    dtype, n, h, w, ci, co, k, s, b, opts = case
+    pad = opts.get("pad", (k - 1) // 2)
+    rng = np.random.Generator(np.random.PCG64(60 + ci + k + s))
+    frames = list(syn.RectVideo(h, w, ci, 3, seed=61 + ci + b, batch=n, n_rect=2, side_lo=5, side_hi=14))
+    wt = rng.normal(0, 0.15, (co, ci, k, k)).astype(np.float32)
+    ho, wo = O.out_size(h, k, s, pad), O.out_size(w, k, s, pad)
+    probe = O.SkipConvOracle(weight_storage(wt, dtype), n=n, h=h, w=w, stride=s, pad=pad, eps=0.0, block=b, dtype=dtype,
+                             **{a: v for a, v in opts.items() if a in ("norm_p", "support", "gate")})
+    stats = [probe.step(syn.to_storage(f, dtype))["stat"] for f in frames[:2]]
+    norm_p = opts.get("norm_p", 2)
+    # (the threshold is on the statistic times the weight norm, to the power p for the output-norm gate)
+    eps = eps_for_density(stats[1:], b, ho, wo, 0.3, norm_p)
+    if opts.get("gate") == "output":
+        eps = eps * (probe.wnorm ** 0.5 if norm_p == 2 else probe.wnorm)
+    keep = opts.get("keep_stats", True)
+    layer, orc = _layer_pair(wt, n=n, h=h, w=w, dtype=dtype, eps=eps, block=b, stride=s, **{"keep_stats": True, **opts})
+    assert layer.fused_variant == 6
+    for t, f in enumerate(frames):
+        xs = syn.to_storage(f, dtype)
+        say(f"[tile options {case}] frame {t}")
+        before = layer._z.clone() if t else None
+        layer.step(to_device(xs, dtype))
+        ref = orc.step(xs)
+        if opts.get("force_dense"):  # the oracle gates: the masks differ, and z by what its eps holds back
+            torch.cuda.synchronize()
+            assert layer.block_mask().all() and layer.site_mask().all()
+            assert np.array_equal(layer.stat().view(np.uint32), ref["stat"].view(np.uint32))
+            continue
+        compare_frame(layer, ref, dtype, t=t, tag=f"tile options {case}", keep_stats=keep)
+        if t:
+            assert 0 < ref["count"] < ref["block_mask"].size, "the gate decides nothing"
+            _check_off_blocks(before, layer, ref["block_mask"], b)
+    layer.close()
 
 
 def _distance(layer, frames, wt, k, s, dtype):
