@@ -222,7 +222,7 @@ ROUTES = [
     (1, 100, 100, 128, 128, 3, 1, 8, False, 3), (1, 128, 128, 128, 96, 3, 1, 4, False, 3),
     (1, 128, 128, 32, 128, 3, 1, 8, False, 3), (1, 160, 160, 32, 128, 3, 1, 8, False, 6),
     (1, 200, 200, 96, 32, 3, 1, 8, False, 1), (1, 200, 200, 96, 128, 1, 1, 8, False, 1), (1, 200, 200, 96, 96, 3, 1, 8, False, 6),
-    (1, 400, 400, 64, 128, 1, 1, 8, True, 0), (1, 400, 400, 32, 128, 3, 1, 16, True, 0), (1, 400, 400, 64, 128, 3, 1, 8, True, 6),
+    (1, 400, 400, 64, 128, 1, 1, 8, True, 0), (1, 400, 400, 32, 128, 3, 1, 16, True, 6), (1, 400, 400, 64, 128, 3, 1, 8, True, 6),
     (1, 400, 400, 48, 80, 1, 1, 8, False, 0), (2, 300, 300, 200, 64, 3, 2, 4, False, 0), (1, 400, 400, 104, 152, 1, 1, 8, False, 6),
 ]
 
