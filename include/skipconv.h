@@ -196,12 +196,15 @@ int skipconv_create(const skipconv_desc* d, const void* weights, void* workspace
  *          sparse convolution kernel, which walks only the listed blocks
  *          (residual halo in LDS, MFMA product, z accumulate).
  *   tile:  one kernel per frame on larger tiles (skipconv_pipeline: 6); also
- *          the reference frames and translated steps of split layers it is
- *          built for.
+ *          reference frames and translated steps of split layers it is built
+ *          for (see skipconv_pipeline).
  * fused is chosen for shapes it is built for whose frames have at most four
- * tiles per compute unit (the variant with weights staged in LDS only for
- * layers of <= 64 input and output channels on at most one tile per compute
- * unit, three for 32 -> 32); SKIPCONV_FLAG_SPLIT_PIPELINE forces split. */
+ * workgroups per compute unit (16 x 16-site tiles with weights staged in LDS:
+ * only layers of <= 64 input and output channels on at most one tile per
+ * compute unit, three for 32 -> 32). From one to three workgroups per compute
+ * unit on, by channels, kernel size and stride, the tile kernel takes over
+ * where it is built for the layer and measured ahead.
+ * SKIPCONV_FLAG_SPLIT_PIPELINE forces split. */
 int skipconv_step(skipconv_t h, const void* x_t, void* stream, const float** z_t);
 
 /* Process one frame whose content moved by (dy, dx) input pixels since the
@@ -218,7 +221,8 @@ int skipconv_step(skipconv_t h, const void* x_t, void* stream, const float** z_t
  * plain skipconv_step. The layer needs SKIPCONV_FLAG_TRANSLATE (E_STATE
  * otherwise). Layers on the single-pass register-operand kernel take the
  * translated step in that kernel (the exposed blocks in a second product over
- * the same weights); the others run the split pipeline. z moves to the other
+ * the same weights), and so do bf16 layers with a norm gate that the one-launch
+ * tile kernel is built for; the others run the split pipeline. z moves to the other
  * of its two slots, so use the returned pointer. */
 int skipconv_step_translated(skipconv_t h, const void* x_t, int32_t dy, int32_t dx, void* stream,
                              const float** z_t);
@@ -306,10 +310,18 @@ int skipconv_get_desc(skipconv_t h, skipconv_desc* d);
  * single-pass kernel for few input channels (fp32 C_in <= 16 or bf16
  * C_in < 8, C_out <= 64, blocks of <= 8: element halo loads, MFMA product
  * with the residual operand gathered per k index), 6 for the one-launch tile
- * kernel (mid-size frames of bf16 layers with 32, 64 or 128 input channels and
- * blocks of 1, 2, 4, 8 or 16: gate of a tile of 8 x 16 or 16 x 16 sites and the
- * product of its active blocks in one workgroup). Reference frames and
- * translated steps of such layers take that kernel also where this reports 0.
+ * kernel: the gate of a tile and the product of its active blocks in one
+ * workgroup, blocks a power of two, C_out % 4 == 0, no residual emission.
+ *   bf16, C_in a multiple of 32 up to 128 or another multiple of 8 from 16 to
+ *   248: tiles of 16 x 16, 8 x 16 or (C_in other than 32, 64, 128) 8 x 8 sites,
+ *   blocks of at most 16; norm gates, and the learned gate with C_in 32 or 64
+ *   and k = 1 or 3.
+ *   fp32, C_in a multiple of 8 from 24 to 128: 8 x 8-site tiles, blocks of at
+ *   most 8, norm gates.
+ * Where 0 is reported, reference frames of such layers take that kernel too
+ * (16 x 16 blocks with C_in <= 64 and more than 64 output channels: only up to
+ * two tiles per compute unit), and so do translated steps of bf16 layers with a
+ * norm gate.
  * Host only. */
 int skipconv_pipeline(skipconv_t h, int32_t* fused);
 

@@ -1,13 +1,16 @@
 // Block-halo MFMA convolution of one tile of output sites (Eq. 3 over the
 // active sites, as the im2col product of Sec. 4.2 restricted to one block):
 // the per-tile work of the split pipeline's convolution kernel, which walks
-// the work list. bf16 operands, fp32 accumulation, C_in % 32 == 0.
+// the work list, and the product of the one-launch tile kernel. bf16 operands,
+// fp32 accumulation, C_in % 32 == 0 (TAB: C_in % 8 == 0).
 //
-// A tile is `tr` output rows x b columns of one block. Per tile:
+// A tile is `tr` output rows x b columns of one block (tile kernel: rows x side
+// sites of any blocks, MASK: those of active ones are stored). Per tile:
 //   1. the accumulators start from z_{t-1} of the tile's sites (0 on a
 //      reference frame), loaded straight into the MFMA output layout (a lane
 //      holds 4 consecutive output channels of one site: z moves in 16-byte
-//      pieces);
+//      pieces); the tile kernel starts them from 0 and adds z_{t-1} after the
+//      product;
 //   2. the input halo ((tr-1)s+k rows x (b-1)s+k columns x C_in) is loaded
 //      with 16-byte loads of both frames, turned into rho = bf16(x_t - x_{t-1})
 //      and stored in LDS with a pixel stride of 2*C_in + 16 bytes (16

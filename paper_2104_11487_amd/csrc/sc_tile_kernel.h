@@ -75,9 +75,10 @@ tile_kernel(GateParams g, ConvParams c, HaloParams hp) {
   float* a_halo = reinterpret_cast<float*>(lds + hp.lds_bytes);
   float* part = reinterpret_cast<float*>(lds + hp.part_off);
 
-  // runs of four tiles dealt to the XCDs: against contiguous ranges 512 x 512 x
-  // 64 per-site 36.4 -> 32.6 us, 256 x 256 x 64 17.3 -> 15.4 us (active tiles
-  // cluster); single tiles lose part of the halo's reuse (37.3 us)
+  // runs of four tiles dealt to the XCDs: active tiles cluster, so contiguous
+  // ranges leave XCDs idle (512 x 512 x 64, per-site, 15 % covered, caller's frames:
+  // 38.3 -> 35.8 us; 2 x 256 x 256 x 64, reference 23.2 -> 22.7, learned 31.3 -> 30.9;
+  // 108 tiles of 135 x 181 11.85 -> 12.0)
   const int tile = xcd_deal<4>(blockIdx.x, gridDim.x);
   const int per_img = g.tiles_y * g.tiles_x;
   const int n = tile / per_img, trem = tile - n * per_img;
