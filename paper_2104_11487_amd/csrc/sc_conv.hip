@@ -266,8 +266,11 @@ __global__ void __launch_bounds__(kConvThreads) conv_bf16_kernel(ConvParams p) {
 // y_old is loaded with z_{t-1}. MODE kTrans: a translated step; the grid also
 // moves the state of the blocks that are off. (Modes of their own, so that the
 // plain step carries neither's code: with the translated step's in it, the
-// 8 x 8-block build of 64 channels measured 3 % slower.)
-enum HaloMode { kPlain, kEmit, kTrans };
+// 8 x 8-block build of 64 channels measured 3 % slower.) kLate (128 output
+// channels): the sums start from 0 and join z_{t-1} after the product, one
+// rounding of the update on the state as in the one-launch tile kernel; without
+// PZ z_{t-1} is loaded then, since it would not fit beside the sums.
+enum HaloMode { kPlain, kEmit, kTrans, kLate };
 template <int WAVES_M, int WAVES_N, int WM, int WN, int KR, bool PZ, int OCC, int KU, int ADB, int MODE>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) __attribute__((amdgpu_waves_per_eu(MODE == kEmit && OCC > 2 ? 2 : OCC)))
 conv_halo_kernel(ConvParams p, HaloParams hp) {
@@ -308,7 +311,7 @@ conv_halo_kernel(ConvParams p, HaloParams hp) {
   for (; tw.t < tw.end; tw.t += tw.step) {
     typename HC::Acc acc;
     typename HC::Yv yo;
-    if constexpr (!PZ) H.load_z(acc, T, false);  // in flight with the halo loads
+    if constexpr (!PZ && MODE != kLate) H.load_z(acc, T, false);  // in flight with the halo loads
     if constexpr (!PZ && EMIT) H.load_y(yo, T, false);
     H.load_halo(T);
     if constexpr (PZ) {
@@ -316,12 +319,30 @@ conv_halo_kernel(ConvParams p, HaloParams hp) {
       for (int i = 0; i < WM; ++i)
 #pragma unroll
         for (int jn = 0; jn < WN; ++jn) {
-          acc[i][jn] = zn[i][jn];
+          if constexpr (MODE != kLate) acc[i][jn] = zn[i][jn];
           if constexpr (EMIT) yo[i][jn] = yn[i][jn];
         }
     }
+    if constexpr (MODE == kLate) {
+#pragma unroll
+      for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int jn = 0; jn < WN; ++jn) acc[i][jn] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
     __syncthreads();
     H.product(acc);
+    if constexpr (MODE == kLate) {
+      if constexpr (!PZ) {
+        asm volatile("" ::: "memory");  // not moved up into the product's registers
+        H.load_z(zn, T, false);
+      }
+#pragma unroll
+      for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int jn = 0; jn < WN; ++jn)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) acc[i][jn][v] = __fadd_rn(zn[i][jn][v], acc[i][jn][v]);
+    }
     // all waves are done with the halo: the next tile may overwrite it
     __syncthreads();
     const bool more = tw.t + tw.step < tw.end;
@@ -758,6 +779,15 @@ hipError_t launch_conv_f32(const ConvParams& p, int grid, hipStream_t st) {
   return hipGetLastError();
 }
 
+using HaloKernel = void (*)(ConvParams, HaloParams);
+// the kLate build of a layer that asks for it, else null
+template <int WAVES_M, int WAVES_N, int WM, int WN, int KR, bool PZ, int OCC, int KU, int ADB>
+HaloKernel late_fn(const HaloParams& hp) {
+  if constexpr (WAVES_N * WN == 8)
+    if (hp.late) return conv_halo_kernel<WAVES_M, WAVES_N, WM, WN, KR, PZ, OCC, KU, ADB, kLate>;
+  return nullptr;
+}
+
 template <int WAVES_M, int WAVES_N, int WM, int WN, int KR, bool PZ, int OCC, int KU, int ADB>
 hipError_t launch_halo_t(const ConvParams& p, const HaloParams& hp, int grid, hipStream_t st) {
   const dim3 g(grid), b(64 * WAVES_M * WAVES_N);
@@ -767,6 +797,8 @@ hipError_t launch_halo_t(const ConvParams& p, const HaloParams& hp, int grid, hi
   else if (p.zsrc)
     hipLaunchKernelGGL((conv_halo_kernel<WAVES_M, WAVES_N, WM, WN, KR, PZ, OCC, KU, ADB, kTrans>), g, b, hp.lds_bytes,
                        st, p, hp);
+  else if (late_fn<WAVES_M, WAVES_N, WM, WN, KR, PZ, OCC, KU, ADB>(hp))
+    hipLaunchKernelGGL((late_fn<WAVES_M, WAVES_N, WM, WN, KR, PZ, OCC, KU, ADB>(hp)), g, b, hp.lds_bytes, st, p, hp);
   else
     hipLaunchKernelGGL((conv_halo_kernel<WAVES_M, WAVES_N, WM, WN, KR, PZ, OCC, KU, ADB, kPlain>), g, b, hp.lds_bytes,
                        st, p, hp);
@@ -787,6 +819,7 @@ template <int WAVES_M, int WAVES_N, int WM, int WN, int KR, bool PZ, int OCC, in
 int halo_occ_t(const HaloParams& hp) {
   auto fn = hp.emit ? conv_halo_kernel<WAVES_M, WAVES_N, WM, WN, KR, PZ, OCC, KU, ADB, kEmit>
                     : conv_halo_kernel<WAVES_M, WAVES_N, WM, WN, KR, PZ, OCC, KU, ADB, kPlain>;
+  if (HaloKernel late = late_fn<WAVES_M, WAVES_N, WM, WN, KR, PZ, OCC, KU, ADB>(hp)) fn = late;
   auto tr = conv_halo_kernel<WAVES_M, WAVES_N, WM, WN, KR, PZ, OCC, KU, ADB, kTrans>;
   for (auto f : {fn, tr})
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -175,6 +175,7 @@ struct HaloParams {
   int lds_bytes;         // hh * hw * pstride
   int threads;           // workgroup size
   int emit;              // the epilogue also writes the successor's residual (bf16, C_out % 8 == 0)
+  int late;              // the sums join z_{t-1} after the product (builds of 128 output channels)
   int rows;              // one-launch tile kernel: output rows of a tile
   int lg_group;          // one-launch tile kernel: log2 of the lanes that hold a pixel's chunks
   int tab_off;           // one-launch tile kernel: LDS offset of the chunk table (C_in not 32, 64, 128), else 0

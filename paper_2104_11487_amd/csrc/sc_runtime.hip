@@ -317,6 +317,7 @@ int derive(const skipconv_desc* d, Geometry* g, char* err) {
     // r32 pieces of 4 channels, whole 8-channel groups for the clears)
     H.emit = (d->flags & SKIPCONV_FLAG_EMIT_RESIDUAL) && d->c_out % 8 == 0 ? 1 : 0;
     H.tiles_per_block = b / H.tr;
+    H.late = 0;
     H.hh = (H.tr - 1) * s + k;
     H.side = b;
     H.hw = (b - 1) * s + k;
@@ -397,15 +398,17 @@ int derive(const skipconv_desc* d, Geometry* g, char* err) {
     // 300 x 300, 128 -> 32 / 128: 42.0 -> 24.6, 47.3 -> 31.1 us; 2 x 500 x 500
     // 128 -> 128, 5 % covered: 125.5 -> 122.6), fewer only up to 64 outputs (1 x 1
     // 64 -> 128, 300 x 500: 21.8 against 24.3 us by the gathering convolution).
-    // (Learned gates of 1 x 1 layers have too little of that work for the 16 x 16
-    // tiles of 128 output channels: 64 -> 128, 400 x 400, 25.1 against 33.0 us, 2 x
-    // 512 x 512 57.9 against 69.3; 320 x 320, 8 x 16 tiles, 23.6 against 21.5. With
-    // 16 x 16 blocks 3 x 3 layers lose too, 39.4 against 51.0, but the block-halo
-    // convolution leaves z 1.35 times as far from the exact sums: they stay.)
-    const bool learned = G.learned && !(G.ntn >= 8 && H.rows == 16 && k == 1 && tiles16 > 3 * kCuGuess / 2);
+    // (Learned gates of 1 x 1 layers and of 16 x 16 blocks have too little of that
+    // work for the 16 x 16 tiles of 128 output channels, split / tile: 64 -> 128,
+    // 400 x 400, 1 x 1, 23.5 / 33.0 us, 3 x 3 with 16 x 16 blocks 38.9 / 51.0; 320 x 320,
+    // 8 x 16 tiles, 23.6 / 21.5. Their block-halo convolution adds z_{t-1} after
+    // the product too, so z is as close to the exact sums: 1.5e-7 of its norm,
+    // 2.0e-7 where the sums start from z_{t-1}.)
+    const bool learned = G.learned && !(G.ntn >= 8 && H.rows == 16 && (k == 1 || b > 8) && tiles16 > 3 * kCuGuess / 2);
     G.tile_plain = G.tile && (learned || (mixed && !gate_bound) ||
                               (!mixed && d->c_in <= 64 && (G.ntn == 2 || G.ntn == 4) && (tiles16 <= 2 * kCuGuess || b < 8)) ||
                               (b < 8 && d->c_in == 128 && G.ntn >= 2 && 2 * tiles16 > kCuGuess));
+    if (G.halo) G.hp.late = G.tile && G.learned && !learned;
   }
 
   // fp32 layers of 24 to 128 channels: 8 x 8-site tiles, norm gates

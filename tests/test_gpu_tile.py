@@ -165,10 +165,12 @@ def test_tile_kernel_f32(case):
 LEARNED = [(1, 181, 187, 64, 64, 3, 8), (1, 150, 141, 32, 20, 3, 1), (3, 170, 171, 64, 64, 3, 16), (1, 41, 70, 64, 12, 3, 16),
            (1, 37, 50, 32, 8, 3, 4), (1, 190, 180, 64, 128, 1, 4), (2, 150, 170, 64, 100, 3, 2), (1, 190, 181, 32, 32, 1, 8),
            (9, 128, 128, 32, 12, 3, 2)]  # one thread per site: the clearing of the flags needs a barrier of its own
+# ... and the split pipeline again, whose block-halo convolution of each block size then adds z_{t-1} after the product
+LEARNED_SPLIT = [(1, 370, 360, 32, 68, 1, 4), (1, 370, 360, 32, 128, 1, 8), (2, 300, 290, 32, 100, 3, 16)]
 
 
 @pytest.mark.parametrize("stats", [True, False], ids=["stats", "nostats"])
-@pytest.mark.parametrize("case", LEARNED, ids=["x".join(map(str, c)) for c in LEARNED])
+@pytest.mark.parametrize("case", LEARNED + LEARNED_SPLIT, ids=["x".join(map(str, c)) for c in LEARNED + LEARNED_SPLIT])
 def test_tile_kernel_learned_gate(case, stats):
     n, h, w, ci, co, k, b = case
     if not stats and n * h * w > 10000 and n < 9:
@@ -179,7 +181,7 @@ def test_tile_kernel_learned_gate(case, stats):
     phi = rng.normal(0, 1.0 / np.sqrt(ci * k * k), (ci, k, k)).astype(np.float32)
     layer, orc = _layer_pair(wt, n=n, h=h, w=w, dtype="bf16", eps=0.0, block=b, gate="learned", phi=phi, gate_bias=-0.25,
                              act_out="identity", keep_stats=stats)
-    assert layer.fused_variant == 6, (case, layer.fused_variant)
+    assert layer.fused_variant == (0 if case in LEARNED_SPLIT else 6), (case, layer.fused_variant)
     for t, f in enumerate(frames):
         if t == 3:
             layer.reset()
@@ -222,7 +224,7 @@ ROUTES = [
     (1, 100, 100, 128, 128, 3, 1, 8, False, 3), (1, 128, 128, 128, 96, 3, 1, 4, False, 3),
     (1, 128, 128, 32, 128, 3, 1, 8, False, 3), (1, 160, 160, 32, 128, 3, 1, 8, False, 6),
     (1, 200, 200, 96, 32, 3, 1, 8, False, 1), (1, 200, 200, 96, 128, 1, 1, 8, False, 1), (1, 200, 200, 96, 96, 3, 1, 8, False, 6),
-    (1, 400, 400, 64, 128, 1, 1, 8, True, 0), (1, 400, 400, 32, 128, 3, 1, 16, True, 6), (1, 400, 400, 64, 128, 3, 1, 8, True, 6),
+    (1, 400, 400, 64, 128, 1, 1, 8, True, 0), (1, 400, 400, 32, 128, 3, 1, 16, True, 0), (1, 400, 400, 64, 128, 3, 1, 8, True, 6),
     (1, 400, 400, 48, 80, 1, 1, 8, False, 0), (2, 300, 300, 200, 64, 3, 2, 4, False, 0), (1, 400, 400, 104, 152, 1, 1, 8, False, 6),
 ]
 
@@ -442,4 +444,24 @@ def test_tile_kernel_f32_is_as_exact_as_the_gathering_convolution(case):
         layer.close()
     say(f"[tile f32 distance {case}] {got}")
     assert got[0][0] == 0 and got[1][0] == 6
+    assert got[1][1] <= 1.03 * got[0][1], got
+
+
+# (c_in, c_out, k, block): the block-halo convolution of a learned layer on many tiles, against the tile kernel on few
+@pytest.mark.parametrize("case", [(64, 128, 1, 4), (64, 128, 1, 8), (64, 128, 3, 16), (32, 96, 3, 16)],
+                         ids=lambda c: "x".join(map(str, c)))
+def test_learned_layers_of_the_split_pipeline_are_as_exact_as_in_the_tile_kernel(case):
+    """As the first of these tests; sums that start from z_{t-1} are 1.1 (1 x 1) to 1.35 times as far."""
+    ci, co, k, b = case
+    g = torch.Generator().manual_seed(23 + ci + co)
+    wt = (torch.randn(co, ci, k, k, generator=g) * (2.0 / (k * k * ci)) ** 0.5).bfloat16()
+    got = []
+    for h in (208, 400):
+        frames = [torch.rand(1, h, h, ci, generator=g).bfloat16() for _ in range(2)]
+        layer = S.SkipConv(wt.cuda(), n=1, h=h, w=h, block=b, gate="learned")
+        layer.set_gate_weights(torch.zeros(ci, k, k).cuda(), 1.0)  # every site on
+        got.append((layer.fused_variant, _distance(layer, frames, wt, k, 1, "bf16")))
+        layer.close()
+    say(f"[learned distance {case}] {got}")
+    assert got[0][0] == 6 and got[1][0] == 0
     assert got[1][1] <= 1.03 * got[0][1], got
