@@ -36,13 +36,14 @@ constexpr int kSide = 8;  // sites per tile side
 constexpr int kItems = 4;
 constexpr int kNonTemporal = 2;
 
-template <int NS>
-__global__ void __launch_bounds__(kF32Threads) __attribute__((amdgpu_waves_per_eu(3)))
+// kParts: partial sums per output
+template <int NS, int kParts>
+__global__ void __launch_bounds__(kF32Threads) __attribute__((amdgpu_waves_per_eu(kParts == 2 ? 4 : 3)))
 tile_f32_kernel(GateParams g, ConvParams c, TileF32Params tp) {
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   __shared__ uint32_t blk_flag[kSide * kSide];
   constexpr int kRing = NS == 4 ? 3 : (NS == 2 ? 4 : 6);  // weight groups in registers
-  constexpr int kParts = 4;                               // partial sums per output
+  constexpr int kJoins = 8 / kParts;                      // times that the partial sums join the total
   const int hh = tp.hh, hw = tp.hw;
   float* a_halo = reinterpret_cast<float*>(lds + hh * hw * tp.pstride);
 
@@ -187,10 +188,14 @@ tile_f32_kernel(GateParams g, ConvParams c, TileF32Params tp) {
   const auto zrs = frame_rsrc(c.z + (size_t)n * zimg, (uint32_t)(zimg * 4));
   uint32_t zoff[NS];
   // kParts partial sums per output, K taken in turn: independent MFMA chains, and
-  // fewer roundings behind each other. They join the total halfway through K and
-  // at its end, so z is no further from the exact sums than by the gathering
+  // fewer roundings behind each other. They join the total kJoins times on the
+  // way through K, so z is no further from the exact sums than by the gathering
   // convolution's four sums over a quarter of K each (relative 2-norm, 2 x 160 x 160,
-  // 128 -> 64: 2.3e-7 against 3.1e-7; two parts 4.6e-7, four without the join 3.2e-7)
+  // 128 -> 64: 2.3e-7 against 3.1e-7; two parts without joins 4.6e-7). Four column
+  // tiles take two parts and four joins where K is long enough for them: four
+  // parts leave registers for three waves per SIMD (256 x 256, 64 -> 64, 3 x 3, 3 %
+  // covered: 33.0 against 25.5 us, 30 % 43.8 against 50.6; the other sizes and
+  // reference frames 1 to 3 % slower on average)
   floatx4 zo[NS], acc[kParts][NS], tot[NS];
 #pragma unroll
   for (int i = 0; i < NS; ++i) {
@@ -202,12 +207,17 @@ tile_f32_kernel(GateParams g, ConvParams c, TileF32Params tp) {
     for (int e = 0; e < kParts; ++e) acc[e][i] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
     tot[i] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
   }
+  auto sum_of_parts = [&](int i, int v) {
+    const float u = __fadd_rn(acc[0][i][v], acc[1][i][v]);
+    if constexpr (kParts == 4) return __fadd_rn(u, __fadd_rn(acc[2][i][v], acc[3][i][v]));
+    return u;
+  };
   auto join = [&]() {
 #pragma unroll
     for (int i = 0; i < NS; ++i) {
 #pragma unroll
       for (int v = 0; v < 4; ++v)
-        tot[i][v] = __fadd_rn(tot[i][v], __fadd_rn(__fadd_rn(acc[0][i][v], acc[1][i][v]), __fadd_rn(acc[2][i][v], acc[3][i][v])));
+        tot[i][v] = __fadd_rn(tot[i][v], sum_of_parts(i, v));
 #pragma unroll
       for (int e = 0; e < kParts; ++e) acc[e][i] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
     }
@@ -238,16 +248,20 @@ tile_f32_kernel(GateParams g, ConvParams c, TileF32Params tp) {
     a = an;
   };
   int j = 0;
-  const int mid = max(groups / 2 / kRing, 1) * kRing;
+  const int run = max(groups / kJoins / kRing, 1) * kRing;  // groups between joins
+  int next = run;
   for (; j + kRing <= groups; j += kRing) {
-    if (j == mid) join();
+    if (j == next) {
+      join();
+      next += run;
+    }
 #pragma unroll
     for (int r = 0; r < kRing; ++r) {
       load_w(wq[(r + kRing - 1) % kRing], min(j + r + kRing - 1, groups - 1));
       use(wq[r]);
     }
   }
-  if (j == mid) join();  // one turn
+  if (j == next) join();
 #pragma unroll
   for (int r = 0; r < kRing - 1; ++r)
     if (r < groups - j) use(wq[r]);
@@ -281,8 +295,10 @@ __global__ void pack_tile_f32_kernel(const float* w, float* out, int c_out, int 
 }
 
 using Kernel = void (*)(GateParams, ConvParams, TileF32Params);
-Kernel kernel_of(int ns) {
-  return ns == 1 ? tile_f32_kernel<1> : (ns == 2 ? tile_f32_kernel<2> : (ns == 4 ? tile_f32_kernel<4> : nullptr));
+Kernel kernel_of(const TileF32Params& t) {
+  // two parts: at least one turn of the weight ring between joins
+  if (t.ns == 4) return t.groups >= 12 ? tile_f32_kernel<4, 2> : tile_f32_kernel<4, 4>;
+  return t.ns == 1 ? tile_f32_kernel<1, 4> : (t.ns == 2 ? tile_f32_kernel<2, 4> : nullptr);
 }
 int lds_of(const TileF32Params& t) { return t.hh * t.hw * t.pstride + (t.hh * t.hw * 4 + 15) / 16 * 16; }
 
@@ -308,7 +324,7 @@ bool tile_f32_shape(TileF32Params& t, int c, int k, int stride, int ntn, long ti
 }
 
 int tile_f32_occupancy(const TileF32Params& t) {
-  const Kernel f = kernel_of(t.ns);
+  const Kernel f = kernel_of(t);
   int blocks = 0;
   if (!f || hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize, lds_of(t)) !=
                 hipSuccess ||
@@ -318,7 +334,7 @@ int tile_f32_occupancy(const TileF32Params& t) {
 }
 
 hipError_t launch_tile_f32(const GateParams& g, const ConvParams& c, const TileF32Params& t, hipStream_t st) {
-  const Kernel f = kernel_of(t.ns);
+  const Kernel f = kernel_of(t);
   if (!f) return hipErrorInvalidValue;
   const int tiles = g.n * g.tiles_y * g.tiles_x;
   hipLaunchKernelGGL(f, dim3((unsigned)((t.deal ? (tiles + 7) / 8 * 8 : tiles) * t.shares)), dim3(kF32Threads), lds_of(t), st, g, c, t);
